@@ -111,6 +111,15 @@ __device__ __forceinline__ float silu(float y) {
 // 1 / sqrt(x) with the hardware reciprocal square root (1 ulp)
 __device__ __forceinline__ float rsqrt_hw(float x) { return __builtin_amdgcn_rsqf(x); }
 
+// x as a value the compiler cannot see through: addresses
+// derived from it are computed where they are used instead of being hoisted
+// out of a loop and held in registers across it (which spills, and a
+// spill reload waits for every vector memory operation issued before it).
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // ---------------------------------------------------------------------------
 // Cross-lane sums with DPP (VALU-rate, no LDS round trip).
 // ---------------------------------------------------------------------------
@@ -347,7 +356,9 @@ int launch_verify(const VerifyArgs& a, hipStream_t stream);
 // trees of 129..512 slots: fp16 features into the workspace, then the
 // pull-back (the workspace holds large_workspace_bytes(...) bytes)
 size_t large_workspace_bytes(int B, int T, int Hk, int Hv, int dk, int dv);
-int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
+// the depth-first order of the trees, kept behind the features
+size_t large_order_bytes(int B);
+int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, void* ord, hipStream_t stream);
 // A device buffer of at least bytes for work on stream, cached per (device,
 // stream) and grown on demand (never while the stream is being captured).
 void* stream_workspace(size_t bytes, hipStream_t stream, int* rc);

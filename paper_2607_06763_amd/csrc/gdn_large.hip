@@ -18,16 +18,28 @@
 //                 magnitude in [1, 2), the inverse scale kept in
 //                 Vs[B][T][Hv]).  The chunked form reads the same features
 //                 as fp32 (launch_features).
+//                 The last blocks of the launch compute each tree's
+//                 depth-first order.
 //   pull_kernel   one workgroup per (value head, sequence), 512 threads:
 //                 the head's S0 as one fp16 plane in LDS (each row scaled by
 //                 the power of two that puts its largest magnitude in [1, 2),
-//                 exact, undone on the output), then tiles of 32 positions:
-//                 16 lanes per node walk the paths with the features of the
-//                 path nodes gathered from FH (fp16 operands into fp32
-//                 accumulators by mixed-precision FMAs), the value heads of
-//                 one key head on one XCD so that they share its k~ rows in
-//                 L2, r x -> an fp16 tile, O^T = S0 (r X)^T on
-//                 v_mfma_f32_16x16x32_f16 (fp32 accumulation), plus acc.
+//                 exact, undone on the output), then tiles of 16 nodes in
+//                 depth-first order, one wave each: the walks of a tile are
+//                 blocked substitutions on the matrix cores (gdn_pull.h) over
+//                 the tile's own 16 rows and its first node's ancestors, 16 at
+//                 a time; then O^T = S0 (r X)^T on v_mfma_f32_16x16x32_f16.
+//                 The value heads of one key head run on one XCD and share
+//                 its k~ rows in L2.
+//
+// What bounds pull_kernel and why this form: walking the path of every node
+// on the VALU (16 lanes per node) gathered each path row once per node below
+// it, 4.4 GB per launch at 32 trees x 512 slots, 16 / 48 heads of 128, and
+// spent two thirds of its instructions on it.  A tile reads the union of its
+// nodes' paths, its own rows plus one chain, once.  That launch (with the
+// commit of the fused step) went from 503 to 363 us, verification alone at 16
+// x 250 slots, 16 / 32 heads, from 71 to 50 us.  128 registers and 80 KB keep
+// two workgroups on a CU: every variant with more spilled or ran one (the
+// values' accumulators live during the substitutions: 62 spills, 647 us).
 // The fused decode step (Sec. 3.4.2) runs the conv-state shift of the
 // previous step's commit first, the features on the committed conv state,
 // and pull_kernel<..., FUSED>, which commits the previous accepted path into
@@ -38,11 +50,12 @@
 #include <mutex>
 
 #include "gdn_commit_rows.h"
+#include "gdn_pull.h"
 
 namespace gdn {
 
 constexpr int kLT = 512;      // threads of a pull-back workgroup (8 waves)
-constexpr int kLTile = 32;    // positions per readout tile (4 per wave)
+constexpr int kLTile = 16;    // nodes per tile (one wave each)
 constexpr int kLMaxT = 512;   // tree slots supported
 constexpr int kFT = 256;      // threads of a feature workgroup
 
@@ -55,7 +68,10 @@ struct LargeParams {
   float* out;
   float* F;       // fp32 features [B][T][C] (chunked form)
   _Float16* FH;   // fp16 features [B][T][C] (pull-back)
-  float* Vs;      // inverse v~ row scales [B][T][Hv] (pull-back)
+  float* Vs;      // inverse v~ row scales [B][T][Hv] (pull-back), negative: the row holds values that are not finite
+  // depth-first order [B][3][kLMaxT] (pull-back): canonical position and end
+  // of the subtree by depth-first index; path of each 16-node tile
+  int16_t* ord;
   // fused step: the previous step's commit, run by the pull-back on the rows
   // it reads (conv_state above is then the conv state after the commit)
   CommitParams cp;
@@ -68,6 +84,8 @@ static size_t fh_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
 size_t large_workspace_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
   return fh_bytes(B, T, Hk, Hv, dk, dv) + size_t(B) * size_t(T) * size_t(Hv) * sizeof(float);
 }
+
+size_t large_order_bytes(int B) { return size_t(B) * 3 * kLMaxT * sizeof(int16_t); }
 
 size_t features_f32_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
   return size_t(B) * size_t(T) * size_t(2 * Hk * dk + Hv * dv) * sizeof(float);
@@ -148,8 +166,118 @@ __device__ __forceinline__ float group_absmax(float v) {
   return __uint_as_float(u);
 }
 
+// Depth-first order of tree b, children by canonical position: ord[i] is the
+// canonical position of the i-th node, ord[kLMaxT + i] the end of its subtree,
+// ord[2 kLMaxT + 16 j + tau] the indices of the nearest 16 proper ancestors of
+// node 16 j, nearest last (kLMaxT: none).  One workgroup of kFT threads; s: 5
+// kLMaxT ints.  A node's index is the sum over
+// its path, without the root, of 1 + the subtree sizes of the siblings before
+// it (siblings share a depth, so they lie between the start of that depth and
+// the node).
+__device__ __forceinline__ void depth_first_order(const MetaPtrs& m, size_t bt, int T, int nval, int16_t* ord, int* s) {
+  int* s_pp = s;               // parent position, -1 for the root
+  int* s_size = s + kLMaxT;    // subtree size; then the path sums
+  int* s_key = s + 2 * kLMaxT;  // parent position << 16 | subtree size
+  int* s_nx = s + 3 * kLMaxT;  // pointer jumping: 2^r-th ancestor; then the parent's index by index
+  int* s_at = s + 4 * kLMaxT;  // index by position
+  constexpr int NP = kLMaxT / kFT;  // positions per thread
+  const int tid = threadIdx.x;
+  int dep[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int i = u * kFT + tid;
+    dep[u] = i < nval ? m.pdep[bt + i] : -1;
+    const int pp = i < nval ? m.ppos[bt + i] : -1;
+    // a parent comes first (depth order); anything else is corrupt metadata
+    s_pp[i] = pp >= 0 && pp < i ? pp : -1;
+    s_size[i] = 1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int i = u * kFT + tid;
+    for (int a = i < nval ? s_pp[i] : -1; a >= 0; a = s_pp[a]) atomicAdd(&s_size[a], 1);
+  }
+  __syncthreads();
+  int size[NP], sum[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int i = u * kFT + tid;
+    size[u] = s_size[i];
+    s_key[i] = i < nval && s_pp[i] >= 0 ? s_pp[i] << 16 | size[u] : -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int i = u * kFT + tid;
+    const int par = s_pp[i];
+    sum[u] = 0;
+    if (i < nval && par >= 0) {
+      sum[u] = 1;
+      // positions after the parent; other depths have other parents
+      for (int j = (par + 1) & ~3; j < i; j += 4) {
+        const int4 k = *reinterpret_cast<const int4*>(s_key + j);
+        const int kk[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[u] += (kk[e] >> 16) == par && j + e < i ? kk[e] & 0xffff : 0;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    s_size[u * kFT + tid] = sum[u];
+    s_nx[u * kFT + tid] = s_pp[u * kFT + tid];
+  }
+  __syncthreads();
+  for (int span = 1; span < T; span <<= 1) {
+    int nx[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      nx[u] = s_nx[u * kFT + tid];
+      if (nx[u] >= 0) {
+        sum[u] += s_size[nx[u]];
+        nx[u] = s_nx[nx[u]];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      s_size[u * kFT + tid] = sum[u];
+      s_nx[u * kFT + tid] = nx[u];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int i = u * kFT + tid;
+    if (i < nval) {
+      const int at = sum[u] < nval ? sum[u] : nval - 1;  // a permutation of 0 .. nval - 1
+      s_at[i] = at;
+      ord[at] = int16_t(i);
+      ord[kLMaxT + at] = int16_t(at + size[u] < nval ? at + size[u] : nval);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int i = u * kFT + tid;
+    if (i < nval) s_nx[s_at[i]] = s_pp[i] >= 0 ? s_at[s_pp[i]] : -1;
+  }
+  __syncthreads();
+  if (tid < (nval + kLTile - 1) / kLTile) {
+    int a = s_nx[kLTile * tid];
+    for (int tau = kLTile - 1; tau >= 0; --tau) {
+      a = a < kLTile * tid ? a : -1;  // ancestors come first
+      ord[2 * kLMaxT + kLTile * tid + tau] = int16_t(a >= 0 ? a : kLMaxT);
+      a = a >= 0 ? s_nx[a] : -1;
+    }
+  }
+}
+
 // VG = 0: fp32 features into p.F; VG = DV / CPT: fp16 features into p.FH
-// with the v~ rows of each head scaled (inverse scales into p.Vs).
+// with the v~ rows of each head scaled (inverse scales into p.Vs), and, in
+// the last p.B blocks, the depth-first order of each tree into p.ord.
 template <typename TIn, int DK, int VG, int CPT>
 __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int ncb) {
   constexpr bool kHalf = VG > 0;
@@ -157,14 +285,27 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
   // positions per register buffer: 32 registers of raw rows (4 taps each)
   constexpr int kFU = 32 / (int(sizeof(TIn)) * CPT);
   __shared__ int s_tap[kFP][4];  // node of each tap, or -1 - conv-state slot
+  __shared__ __align__(16) float4 s_cs[3][CPT / 4][kFT];  // conv-state slots of the thread's channels
   // Blocks go round-robin over the 8 XCDs.  The grid is one-dimensional and
   // renumbered so that each XCD takes a contiguous range of (position block,
   // channel block, sequence) in that order: the position blocks of one
   // channel block of a sequence run on one XCD, where the rows that some of
   // them load are still in L2 when others gather them as ancestor taps
   // (measured: 1.5x fewer HBM bytes fetched).
-  const int nblk = gridDim.x, per = nblk / 8;
+  const int nblk = kHalf ? gridDim.x - p.B : gridDim.x, per = nblk / 8;
   const int id = blockIdx.x;
+  if constexpr (kHalf) {
+    static_assert(sizeof(s_cs) >= 5 * kLMaxT * sizeof(int), "order LDS");
+    if (id >= nblk) {  // uniform
+      const int b = id - nblk;
+      const MetaPtrs m = meta_ptrs(p.meta, p.B, p.T);
+      const int nval = m.status[b] == GDN_TREE_OK ? m.nvalid[b] : 0;
+      if (nval > 0)
+        depth_first_order(m, size_t(b) * p.T, p.T, nval < p.T ? nval : p.T, p.ord + size_t(b) * 3 * kLMaxT,
+                          reinterpret_cast<int*>(s_cs));
+      return;
+    }
+  }
   const int L = id < 8 * per ? (id % 8) * per + id / 8 : id;
   const int nyb = (p.T + kFP - 1) / kFP;
   const int yb = L % nyb, bx = (L / nyb) % ncb, b = L / (nyb * ncb);
@@ -217,7 +358,6 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
   // the conv-state slots of this thread's channels (taps above the root),
   // kept in LDS: read under a branch, an LDS load does not make the row
   // loads in flight wait
-  __shared__ float4 s_cs[3][CPT / 4][kFT];
   {
     const float* cs = p.conv_state + size_t(b) * 3 * C + c;
 #pragma unroll
@@ -277,9 +417,10 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
         y[j] = silu(fmaf(wv[j].w, x[3][j], fmaf(wv[j].z, x[2][j], fmaf(wv[j].y, x[1][j], wv[j].x * x[0][j]))));
         ss = fmaf(y[j], y[j], ss);
       }
+      const bool odd = kHalf && __any(!(ss < __builtin_inff()));  // squares that overflow, or inf or NaN
       // the DK / CPT lanes of a q or k head are consecutive lanes of one wave
       ss = group_sum<DK / CPT>(ss);
-      const float f = qk ? rsqrt_hw(ss + 1e-6f) : 1.0f;
+      float f = qk ? rsqrt_hw(ss + 1e-6f) : 1.0f;
       const bool st = ok && g0 + u < np;
       if constexpr (kHalf) {
         // v~: one power-of-two scale per (position, head) from the row max
@@ -289,6 +430,16 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
         mx = group_absmax<VG>(mx);
         float sc, inv;
         row_scale(mx, sc, inv);
+        if (odd) {  // wave-uniform, rare
+          float t = 0.0f;
+#pragma unroll
+          for (int j = 0; j < CPT; ++j) t += y[j] * 0.0f;
+          t = t == t ? 0.0f : 1.0f;  // holds inf or NaN
+          // a q or k row with one is NaN throughout; a v row says so by the
+          // sign of its scale
+          if (qk && group_max<DK / CPT>(t) != 0.0f) f = __builtin_nanf("");
+          if (!qk && group_max<(kHalf ? VG : 1)>(t) != 0.0f) inv = -inv;
+        }
         const float g = qk ? f : sc;
         uint2 h4[CPT / 4];
 #pragma unroll
@@ -326,19 +477,21 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
 // ---------------------------------------------------------------------------
 // Pull-back along gathered features + fp16 MFMA readout
 // ---------------------------------------------------------------------------
+// Two workgroups per CU: at most 80 KB each.
 template <int DK, int DV>
 struct PullSmem {
-  static constexpr int KP = (DK < 32 ? 32 : DK) + 8;  // fp16 row (zero beyond DK)
-  static constexpr int PP = DV + 4;                    // fp32 row of the product tile
+  static constexpr int KP = (DK < 32 ? 32 : DK) + 8;  // fp16 row of the state plane (zero beyond DK)
+  static constexpr int KR = DK * 2, VR = DV * 2;       // bytes per row of a chunk
   static constexpr size_t plane = size_t(DV) * KP * 2;
-  static constexpr size_t xt = size_t(2) * kLTile * KP * 2;  // r x as fp16 hi and lo planes
-  static constexpr size_t pt = size_t(kLTile) * PP * 4;
-  // the plane and the two tiles; in the fused step the commit's LDS first
-  static constexpr size_t front = plane + xt + pt > commit_lds_bytes<DK, DV>() ? plane + xt + pt
-                                                                              : commit_lds_bytes<DK, DV>();
+  static constexpr size_t chunk = size_t(kLTile) * (KR > VR ? KR : VR);  // 16 rows of k~ or v~, one per wave
+  // the plane and the chunks; in the fused step the commit's LDS first
+  static constexpr size_t tiles = plane + (kLT / 64) * chunk;
+  static constexpr size_t front = tiles > commit_lds_bytes<DK, DV>() ? tiles : commit_lds_bytes<DK, DV>();
   static constexpr size_t inv = size_t(DV) * 4;
-  static constexpr size_t meta = size_t(kLMaxT) * (2 + 4 + 4 + 4 + 4);
-  static constexpr size_t total = front + inv + meta;
+  static constexpr size_t gates = size_t(kLMaxT + 1) * 16;
+  static constexpr size_t solve = size_t(kLT / 64) * 64 * 4;
+  static constexpr size_t order = size_t(kLMaxT + 8) * 2 * 2 + size_t(kLT / 64) * kLTile * 2;
+  static constexpr size_t total = front + inv + gates + solve + order;
 };
 
 template <int N>
@@ -358,41 +511,77 @@ __device__ __forceinline__ void ld_f(const float* src, float (&x)[N]) {
   }
 }
 
-// N consecutive fp16 values (N = 1, 2, 4, 8, aligned to 2 N bytes) as one
-// load, kept packed in registers.
-template <int N>
-struct HalfVec {
-  typedef _Float16 type __attribute__((ext_vector_type(N)));
+// 16 rows of D halves as A operands in channel order: lane (l16, m) holds
+// channels 32 kb + 8 m .. + 7 of row l16 (zero beyond D = 16).
+template <int D>
+struct RowFrag {
+  static constexpr int KB = D >= 32 ? D / 32 : 1;
+  static constexpr int kMask = D / 16 - 1;  // 32-byte granules of a row, swizzled by the row
+  f16x8 f[KB];
+  __device__ __forceinline__ void load(const _Float16* row, int m) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      if constexpr (D >= 32) {
+        f[kb] = *reinterpret_cast<const f16x8*>(row + 32 * kb + 8 * m);
+      } else {
+        f[kb] = *reinterpret_cast<const f16x8*>(row + 8 * (m & 1));
+        if (m >= 2) f[kb] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      }
+    }
+  }
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) f[kb] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  }
+  // values that are not finite -> 0
+  __device__ __forceinline__ void keep_finite() {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[kb][e] = fabsf((float)f[kb][e]) < 65536.0f ? f[kb][e] : (_Float16)0.0f;
+  }
+  // -> LDS, row l16 at l16 * 2 D bytes
+  __device__ __forceinline__ void store(unsigned char* buf, int l16, int m) const {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+      if (D >= 32 || m < 2)
+        *reinterpret_cast<f16x8*>(buf + l16 * 2 * D + (((2 * kb + (m >> 1)) ^ l16) & kMask) * 32 + 16 * (m & 1)) = f[kb];
+  }
+  // 4 channels 16 t + 4 m .. of row l16 (accumulator slot order)
+  __device__ static __forceinline__ f16x4 slots(const unsigned char* buf, int t, int l16, int m) {
+    return *reinterpret_cast<const f16x4*>(buf + l16 * 2 * D + ((t ^ l16) & kMask) * 32 + 8 * m);
+  }
+  // channel 16 t + l16 of rows 4 m .. 4 m + 3
+  __device__ static __forceinline__ f16x4 columns(const unsigned char* buf, int t, int l16, int m) {
+    const int r = 4 * m + (l16 >> 2);
+    return ld_tr(buf + r * 2 * D + ((t ^ r) & kMask) * 32 + 8 * (l16 & 3));
+  }
 };
-template <int N>
-__device__ __forceinline__ typename HalfVec<N>::type ld_h(const _Float16* src) {
-  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "fp16 vector width");
-  return *reinterpret_cast<const typename HalfVec<N>::type*>(src);
-}
 
-// the same at a 32-bit byte offset from a wave-uniform base (a scalar base
-// plus a vector offset: no 64-bit address arithmetic per load)
-template <int N>
-__device__ __forceinline__ typename HalfVec<N>::type ld_hb(const _Float16* base, uint32_t byte_off) {
-  return *reinterpret_cast<const typename HalfVec<N>::type*>(reinterpret_cast<const char*>(base) + byte_off);
-}
+// Gates of a node for one value head
+struct RowGate {
+  float be, la, vs;  // beta, log2 alpha, inverse v~ row scale (sign: see LargeParams)
+  int end;           // end of the subtree, 0 past the nodes
+};
 
 template <int DK, int DV, typename TIn, bool FUSED>
-__global__ __launch_bounds__(kLT) void pull_kernel(LargeParams p) {
+__global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
   using SM = PullSmem<DK, DV>;
-  constexpr int KP = SM::KP, PP = SM::PP;
-  constexpr int CK = DK / 16, CV = DV / 16;  // channels per lane (16 lanes per node)
-  constexpr int KS = (DK < 32 ? 32 : DK) / 32;
+  using KF = RowFrag<DK>;
+  using VF = RowFrag<DV>;
+  constexpr int KP = SM::KP;
+  constexpr int CK = DK / 16;                 // state columns per lane of the plane set-up
+  constexpr int NX = DK / 16, NV = DV / 16;   // 16-channel tiles
+  constexpr int KB = KF::KB;
+  static_assert(SM::total <= 80 * 1024, "two workgroups per CU");
   extern __shared__ __align__(16) unsigned char smem[];
   _Float16* s_plane = reinterpret_cast<_Float16*>(smem);
-  _Float16* s_x = reinterpret_cast<_Float16*>(smem + SM::plane);  // [2][kLTile][KP]: hi, lo
-  float* s_p = reinterpret_cast<float*>(smem + SM::plane + SM::xt);
   float* s_inv = reinterpret_cast<float*>(smem + SM::front);
-  int* s_ppos = reinterpret_cast<int*>(smem + SM::front + SM::inv);
-  float* s_al = reinterpret_cast<float*>(s_ppos + kLMaxT);
-  float* s_be = s_al + kLMaxT;
-  float* s_vs = s_be + kLMaxT;  // inverse v~ row scales by position
-  int16_t* s_ord = reinterpret_cast<int16_t*>(s_vs + kLMaxT);
+  RowGate* s_g = reinterpret_cast<RowGate*>(s_inv + DV);       // by depth-first index; kLMaxT: no node
+  float* s_solve = reinterpret_cast<float*>(s_g + kLMaxT + 1);  // 64 floats per wave
+  int16_t* s_row = reinterpret_cast<int16_t*>(s_solve + kLT);  // canonical position
+  int16_t* s_path = s_row + kLMaxT + 8;      // nearest ancestors of each tile's first node
+  int16_t* s_list = s_path + kLMaxT + 8;     // 16 path nodes per wave (deeper trees)
 
   // Blocks go round-robin over the 8 XCDs: the G value heads of unit u =
   // (sequence, key head), which gather the same k~ rows, take blocks
@@ -404,30 +593,45 @@ __global__ __launch_bounds__(kLT) void pull_kernel(LargeParams p) {
   if (unit >= p.B * Hk) return;  // uniform
   const int b = unit / Hk, g = unit % Hk, h = g * G + rem / 8;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nq = Hk * DK;
   const size_t C = size_t(2 * nq + Hv * DV);
-  const MetaPtrs m = meta_ptrs(p.meta, p.B, T);
+  const MetaPtrs m_ = meta_ptrs(p.meta, p.B, T);
   const size_t bt = size_t(b) * T;
-  const int nval = m.status[b] == GDN_TREE_OK ? m.nvalid[b] : 0;
+  const int nval = __builtin_amdgcn_readfirstlane(m_.status[b] == GDN_TREE_OK ? m_.nvalid[b] : 0);
   const TIn* alpha = static_cast<const TIn*>(p.alpha);
   const TIn* beta = static_cast<const TIn*>(p.beta);
+  const _Float16* Fb = p.FH + bt * C;
+  const _Float16* Fk = Fb + nq + g * DK;
+  const _Float16* Fv = Fb + 2 * nq + h * DV;
 
-  // ---- tree metadata and this head's gates by position
-  for (int j = tid; j < T; j += kLT) {
-    const int nd = m.order[bt + j];
-    s_ord[j] = int16_t(nd);
-    // a parent sits at a smaller position (depth order); anything else
-    // (corrupt metadata) ends the walk, so every walk terminates
-    const int pp = j < nval ? m.ppos[bt + j] : -1;
-    s_ppos[j] = pp >= 0 && pp < j ? pp : -1;
-    s_al[j] = j < nval ? ld(alpha, (bt + nd) * Hv + h) : 0.0f;
-    s_be[j] = j < nval ? ld(beta, (bt + nd) * Hv + h) : 0.0f;
-    s_vs[j] = j < nval ? p.Vs[(bt + j) * Hv + h] : 0.0f;
+  // ---- order and this head's gates by depth-first index
+  const int16_t* ord = p.ord + size_t(b) * 3 * kLMaxT;
+  for (int j = tid; j <= kLMaxT; j += kLT) {
+    const bool real = j < nval;
+    int row = nval > 0 ? ord[real ? j : nval - 1] : 0;  // past the nodes: the last one's row
+    RowGate g = {0.0f, 0.0f, 0.0f, 0};
+    row = row >= 0 && row < T ? row : 0;
+    if (real) {
+      const int nd = m_.order[bt + row];
+      const float la = __builtin_amdgcn_logf(ld(alpha, (bt + nd) * Hv + h));
+      g.la = la < -512.0f ? -512.0f : la;  // a decay of 0 stays finite, 2^la is 0
+      g.be = ld(beta, (bt + nd) * Hv + h);
+      // a key that is not finite (its row is NaN): beta NaN takes it to the nodes below
+      if (!(fabsf((float)Fk[size_t(row) * C]) < 65536.0f)) g.be = __builtin_nanf("");
+      g.vs = p.Vs[(bt + row) * Hv + h];
+      g.end = ord[kLMaxT + j];
+    }
+    s_g[j] = g;
+    s_row[j] = int16_t(row);
+    if (j < kLMaxT) {
+      const int a = j < ((nval + kLTile - 1) & ~(kLTile - 1)) ? ord[2 * kLMaxT + j] : kLMaxT;
+      s_path[j] = int16_t(a >= 0 && a < kLMaxT ? a : kLMaxT);
+    }
   }
   if constexpr (FUSED) {
     // ---- fused step: the previous step's accepted path is committed into
-    //      this head's rows (its LDS in the plane and tile region), the rows
+    //      this head's rows (its LDS in the plane and chunk region), the rows
     //      go back to S and straight into the fp16 plane
     using CS = CommitSplit<DK, DV, kLT>;
     float srow[CS::EPT];
@@ -444,17 +648,12 @@ __global__ __launch_bounds__(kLT) void pull_kernel(LargeParams p) {
       row_scale(mx, sc, inv);
       const int r = row + i * CS::RS;
 #pragma unroll
-      for (int e = 0; e < CS::CPT; ++e) s_plane[r * KP + col0 + e] = (_Float16)(srow[i * CS::CPT + e] * sc);
-      if (tid % CS::LPR == 0) s_inv[r] = inv;
-    }
-    if constexpr (DK < 32) {
-      for (int i = tid; i < DV * (32 - DK); i += kLT)
-        s_plane[(i / (32 - DK)) * KP + DK + i % (32 - DK)] = (_Float16)0.0f;
-      for (int i = tid; i < 2 * kLTile * (32 - DK); i += kLT)
-        s_x[(i / (32 - DK)) * KP + DK + i % (32 - DK)] = (_Float16)0.0f;
+      for (int e = 0; e < CS::CPT; ++e)
+        s_plane[r * KP + plane_col(col0 + e)] = (_Float16)(srow[i * CS::CPT + e] * sc);
+      if (tid % CS::LPR == 0) s_inv[r] = p.scale * inv;
     }
   } else if (nval > 0) {
-    // ---- S0 -> fp16 plane (16 lanes per row), zero columns past DK
+    // ---- S0 -> fp16 plane (16 lanes per row)
     const float* S0 = p.S0 + (size_t(b) * Hv + h) * size_t(DV) * DK;
     const int ln = tid & 15;
     for (int r0 = 0; r0 < DV; r0 += kLT / 16) {
@@ -469,116 +668,248 @@ __global__ __launch_bounds__(kLT) void pull_kernel(LargeParams p) {
         float sc, inv;
         row_scale(mx, sc, inv);
 #pragma unroll
-        for (int e = 0; e < CK; ++e) s_plane[r * KP + ln * CK + e] = (_Float16)(xs[e] * sc);
-        if (ln == 0) s_inv[r] = inv;
+        for (int e = 0; e < CK; ++e) s_plane[r * KP + plane_col(ln * CK + e)] = (_Float16)(xs[e] * sc);
+        if (ln == 0) s_inv[r] = p.scale * inv;
       }
     }
-    if constexpr (DK < 32) {
-      for (int i = tid; i < DV * (32 - DK); i += kLT)
-        s_plane[(i / (32 - DK)) * KP + DK + i % (32 - DK)] = (_Float16)0.0f;
-      for (int i = tid; i < 2 * kLTile * (32 - DK); i += kLT)
-        s_x[(i / (32 - DK)) * KP + DK + i % (32 - DK)] = (_Float16)0.0f;
-    }
+  }
+  if constexpr (DK < 32) {  // zero columns past DK
+    for (int i = tid; i < DV * (32 - DK); i += kLT)
+      s_plane[(i / (32 - DK)) * KP + plane_col(DK + i % (32 - DK))] = (_Float16)0.0f;
   }
   __syncthreads();
 
-  const float scale = p.scale;
-  const int jn = wave * 4 + (lane >> 4);  // node slot of this lane in a tile
-  const int ln = lane & 15;
-  const _Float16* Fb = p.FH + bt * C;
-  using HK = typename HalfVec<CK>::type;
-  using HVv = typename HalfVec<CV>::type;
-  for (int n0 = 0; n0 < T; n0 += kLTile) {
-    const int pos = n0 + jn;
-    const bool real = pos < nval;
-    float x[CK], acc[CV];
-    float r = 1.0f;
+  // ---- tiles of 16 nodes, one wave each: no barrier below
+  unsigned char* buf = smem + SM::plane + wave * SM::chunk;
+  float* z = s_solve + 64 * wave;
+  int16_t* list = s_list + kLTile * wave;
+  const _Float16 one = (_Float16)1.0f;
+  const f16x8 ones = {one, one, one, one, one, one, one, one};
+  const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+  for (int n0 = kLTile * wave; n0 < T; n0 += kLT / 64 * kLTile) {
+    // lane roles from values that the compiler cannot see through: addresses
+    // are formed where they are used, not hoisted, kept and spilled
+    const int ln = opaque(lane), l16 = ln & 15, m = ln >> 4;
+    const int n = n0 + l16;  // this lane's column
+    // slots of the tile's nodes; the padding ones come in canonical order
+    const int slot = n < T ? m_.order[bt + (n < nval ? int(s_row[n]) : n)] : 0;
+    float* outh = p.out + bt * size_t(Hv) * DV + size_t(h) * DV;  // uniform
+    if (n0 >= nval) {  // uniform
+      if (n < T) {
 #pragma unroll
-    for (int e = 0; e < CV; ++e) acc[e] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < CK; ++e) x[e] = 0.0f;
-    if (real) {
-      {
-        const HK q0 = ld_h<CK>(Fb + size_t(pos) * C + g * DK + ln * CK);
-#pragma unroll
-        for (int e = 0; e < CK; ++e) x[e] = (float)q0[e];
+        for (int t = 0; t < NV; ++t)
+          *reinterpret_cast<float4*>(outh + size_t(slot) * Hv * DV + 4 * m + 16 * t) = make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      // walk to the root.  The gathers of the path rows are what bounds this
-      // loop (L2 / MALL bandwidth, 16 resident waves per CU hide their
-      // latency): loading rows ahead, which past the root means loading
-      // rows that are never used, measured slower.
-      // uniform row bases and a 32-bit lane offset (rows of one sequence
-      // span B T C / B < 2^31 halves)
-      const _Float16* Fk = Fb + nq + g * DK;
-      const _Float16* Fv = Fb + 2 * nq + h * DV;
-      const uint32_t Cu = uint32_t(C);
-      for (int t = pos; t >= 0; t = s_ppos[t]) {  // uniform per 16-lane node group
-        const uint32_t ro = uint32_t(t) * Cu;  // byte offsets below in 32 bits
-        const HK kt = ld_hb<CK>(Fk, 2 * (ro + uint32_t(ln * CK)));
-        const HVv vt = ld_hb<CV>(Fv, 2 * (ro + uint32_t(ln * CV)));
-        float s0 = 0.0f, s1 = 0.0f;  // two chains
-#pragma unroll
-        for (int e = 0; e < CK; e += 2) {
-          s0 = fmaf((float)kt[e], x[e], s0);
-          if (e + 1 < CK) s1 = fmaf((float)kt[e + 1], x[e + 1], s1);
-        }
-        const float s = group_sum<16>(s0 + s1);
-        const float c = s_be[t] * s;
-        const float rc = r * c * s_vs[t];
-#pragma unroll
-        for (int e = 0; e < CV; ++e) acc[e] = fmaf(rc, (float)vt[e], acc[e]);
-#pragma unroll
-        for (int e = 0; e < CK; ++e) x[e] = fmaf(-c, (float)kt[e], x[e]);
-        r *= s_al[t];
-      }
+      continue;
     }
-    // r x -> tile row jn (zero for padding positions) as fp16 hi + lo: the
-    // product takes both, so x contributes no rounding beyond ~2^-22 (with
-    // fp16 features the key dims are short, and an x rounded once to 11 bits
-    // cost up to 3e-4 of max|o| on 16-dim heads)
-#pragma unroll
-    for (int e = 0; e < CK; ++e) {
-      const float rx = r * x[e];
-      const _Float16 hi = (_Float16)rx;
-      s_x[jn * KP + ln * CK + e] = hi;
-      s_x[(kLTile + jn) * KP + ln * CK + e] = (_Float16)(rx - (float)hi);
-    }
-    __syncthreads();
-    // O^T tiles (16 value rows x 16 positions), K = key channels
+    // index of row tau of a chunk: the tile's own (lst null) or a list's
+    auto index = [&](const int16_t* lst, int tau) { return lst ? int(lst[tau]) : n0 + tau; };
+    const float y1 = one_f();
+    f16x8 qf[KB];  // q~ of column l16, channel order
+    f32x4 x[NX], acc[NV];
     {
-      const int l16 = lane & 15, lg = lane >> 4;
-      for (int task = wave; task < (DV / 16) * (kLTile / 16); task += kLT / 64) {
-        const int rt = task / (kLTile / 16), ct = task % (kLTile / 16);
-        f32x4 acc4 = {0.f, 0.f, 0.f, 0.f};
+      const _Float16* q = Fb + size_t(s_row[n]) * C + g * DK;
+      KF t;
+      t.load(q, m);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const f16x8 a = *reinterpret_cast<const f16x8*>(s_plane + (16 * rt + l16) * KP + 32 * ks + 8 * lg);
-          const f16x8 bx = *reinterpret_cast<const f16x8*>(s_x + (16 * ct + l16) * KP + 32 * ks + 8 * lg);
-          const f16x8 bl = *reinterpret_cast<const f16x8*>(s_x + (kLTile + 16 * ct + l16) * KP + 32 * ks + 8 * lg);
-          acc4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bx, acc4, 0, 0, 0);
-          acc4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bl, acc4, 0, 0, 0);
-        }
+      for (int kb = 0; kb < KB; ++kb) qf[kb] = t.f[kb];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 16 * rt + 4 * lg + i;
-          s_p[(16 * ct + l16) * PP + row] = acc4[i] * s_inv[row];
-        }
+      for (int t2 = 0; t2 < NX; ++t2) {
+        const f16x4 q4 = *reinterpret_cast<const f16x4*>(q + 16 * t2 + 4 * m);
+        x[t2] = f32x4{(float)q4[0], (float)q4[1], (float)q4[2], (float)q4[3]};
       }
     }
-    __syncthreads();
-    if (pos < T) {
-      float o[CV];
-#pragma unroll
-      for (int e = 0; e < CV; ++e) o[e] = real ? scale * (s_p[jn * PP + ln * CV + e] + acc[e]) : 0.0f;
-      float* dst = p.out + (bt + s_ord[pos]) * size_t(Hv) * DV + size_t(h) * DV + ln * CV;
-      if constexpr (CV % 4 == 0) {
-#pragma unroll
-        for (int e = 0; e < CV; e += 4)
-          *reinterpret_cast<float4*>(dst + e) = make_float4(o[e], o[e + 1], o[e + 2], o[e + 3]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < CV; ++e) dst[e] = o[e];
+    float lw = 0.0f;  // log2 of the decay of the rows walked
+    // The substitution over one chunk of path nodes: x and lw move up by the
+    // chunk; returns the value coefficients r c / (v~ row scale) of the
+    // accumulator rows.  vmin: below 0 if a v~ row of this lane's is marked.
+    auto solve = [&](const int16_t* lst, float& vmin) -> f32x4 {
+      const bool own = lst == nullptr;
+      const int ln = opaque(lane), l16 = ln & 15, m = ln >> 4;
+      const int il = index(lst, tau_of(l16));
+      KF kf;
+      kf.load(Fk + size_t(s_row[il]) * C, m);
+      const RowGate gl = s_g[il];
+      if (__any(gl.be != gl.be)) {
+        if (gl.be != gl.be) kf.zero();
       }
+      // ---- s = K x, Gram tile
+      f32x4 s = z4, gm = z4;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) gm = mfma_h(kf.f[kb], kf.f[kb], gm);
+      kf.store(buf, l16, m);
+      if (own) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) s = mfma_h(kf.f[kb], qf[kb], s);
+      }
+      wave_lds_order();
+      if (!own) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+          f16x4 h0, l0, h1 = {0, 0, 0, 0}, l1 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
+          split4(x[2 * kb], y1, h0, l0);
+          const f16x4 a0 = KF::slots(buf, 2 * kb, l16, m);
+          if constexpr (NX > 1) {
+            split4(x[2 * kb + 1], y1, h1, l1);
+            a1 = KF::slots(buf, 2 * kb + 1, l16, m);
+          }
+          s = mfma_h(cat(a0, a1), cat(l0, l1), s);
+          s = mfma_h(cat(a0, a1), cat(h0, h1), s);
+        }
+      }
+      // ---- gates of accumulator rows e = 0 .. 3 (rows without a node: end 0)
+      f32x4 bm, la, vs;
+      int ie[4];
+      RowGate ge[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ie[e] = index(lst, 4 * e + m);
+        ge[e] = s_g[ie[e]];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(ge[e].be), "+v"(ge[e].la), "+v"(ge[e].vs));  // loaded, not branched around
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const RowGate g = ge[e];
+        const bool on = ie[e] <= n && n < g.end;
+        bm[e] = on ? g.be : 0.0f;
+        la[e] = on ? g.la : 0.0f;
+        vs[e] = fabsf(g.vs);
+        vmin = fminf(vmin, g.vs);
+      }
+      // N_ij = beta_i k_i.k_j for i above j, in the 4 x 4 block of step l16 %
+      // 4; row il is the block's row i (a chain, or an absent row, beta 0)
+      const bool up = (l16 >> 2) < m && (!own || n0 + 4 * (l16 & 3) + m < gl.end);
+      const float di = block_inverse(z, up ? finite(gl.be) * diag_entry(gm, l16) : 0.0f, l16, m);
+      f16x4 h0, l0;
+      split4(la, y1, h0, l0);
+      const f16x4 an = above_rows(l16, m, own ? gl.end - n0 : kLTile);
+      const f32x4 w0 = {lw, lw, lw, lw};
+      const f32x4 lr = mfma_h(cat(an, an), cat(h0, l0), w0);
+      lw = mfma_h(ones, cat(h0, l0), w0)[0];
+      const f32x4 c = substitute(s, gm, di, bm, l16);
+      __builtin_amdgcn_sched_barrier(0);
+      // ---- x -= K^T c
+      split4(-c, y1, h0, l0);
+#pragma unroll
+      for (int t = 0; t < NX; ++t) {
+        const f16x4 a = KF::columns(buf, t, l16, m);
+        x[t] = mfma_h16(a, l0, x[t]);
+        x[t] = mfma_h16(a, h0, x[t]);
+      }
+      wave_lds_order();
+      f32x4 mm;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mm[e] = c[e] * __builtin_amdgcn_exp2f(lr[e]) * vs[e];
+      return mm;
+    };
+    auto largest = [](f32x4 a) { return fmaxf(fmaxf(fabsf(a[0]), fabsf(a[1])), fmaxf(fabsf(a[2]), fabsf(a[3]))); };
+    // acc = f acc + V^T (scl mm) over the chunk
+    auto values = [&](const int16_t* lst, f32x4 mm, float scl, float f, bool marked) {
+      const int ln = opaque(lane), l16 = ln & 15, m = ln >> 4;
+      VF vf;
+      vf.load(Fv + size_t(s_row[index(lst, tau_of(l16))]) * C, m);
+      f16x4 h0, l0;
+      split4(mm, scl, h0, l0);
+      if (marked) vf.keep_finite();
+      vf.store(buf, l16, m);
+      wave_lds_order();
+#pragma unroll
+      for (int t = 0; t < NV; ++t) {
+        const f16x4 a = VF::columns(buf, t, l16, m);
+        acc[t] = mfma_h16(a, l0, lst ? acc[t] * f : z4);
+        acc[t] = mfma_h16(a, h0, acc[t]);
+      }
+      wave_lds_order();
+      if (marked) {
+        // values that are not finite reach the nodes whose path holds their
+        // row, and no others
+#pragma unroll 1
+        for (int j = 0; j < kLTile; ++j) {
+          const int i = index(lst, j), e = j >> 2;
+          const RowGate g = s_g[i];
+          const float cj =
+              scl * __shfl(e == 0 ? mm[0] : (e == 1 ? mm[1] : (e == 2 ? mm[2] : mm[3])), l16 + 16 * (j & 3));
+          if (i <= n && n < g.end && g.vs < 0.0f) {
+            const _Float16* v = Fv + size_t(s_row[i]) * C + 4 * m;
+#pragma unroll
+            for (int t = 0; t < NV; ++t)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const float y = (float)v[16 * t + q];
+                if (!(fabsf(y) < 65536.0f)) acc[t][q] += cj * y;
+              }
+          }
+        }
+      }
+    };
+    // The first two chunks' values follow both solutions: x and the solver's
+    // registers are then not live together with acc (128 registers allow two
+    // workgroups per CU).
+    const int16_t* path = s_path + n0;
+    const int near = path[kLTile - 1];  // parent of the tile's first node
+    float mrun, inv;              // largest value coefficient, power of two acc is divided by
+    {
+      float va = 0.0f, vb = 0.0f;
+      const f32x4 ma = solve(nullptr, va);
+      f32x4 mb = z4;
+      if (near < kLMaxT) mb = solve(path, vb);
+      mrun = cross_max(fmaxf(largest(ma), largest(mb)));
+      float scl;
+      row_scale(mrun, scl, inv);
+      values(nullptr, ma, scl, 0.0f, __any(va < 0.0f));
+      if (near < kLMaxT) values(path, mb, scl, 1.0f, __any(vb < 0.0f));
+    }
+    if (path[0] < kLMaxT) {
+      // more than 16 ancestors: 16 at a time, found as the nodes before the
+      // tile whose subtree reaches past its first node
+      const int np = m_.pdep[bt + s_row[n0]];
+      for (int base = np - 2 * kLTile; base > -kLTile; base -= kLTile) {
+        if (lane < kLTile) list[lane] = int16_t(kLMaxT);
+        wave_lds_order();
+        for (int a = lane; a < n0; a += 64) {
+          if (s_g[a].end > n0) {
+            const int d = m_.pdep[bt + s_row[a]] - base;
+            if (d >= 0 && d < kLTile) list[d] = int16_t(a);
+          }
+        }
+        wave_lds_order();
+        float vb = 0.0f;
+        const f32x4 mb = solve(list, vb);
+        mrun = fmaxf(mrun, cross_max(largest(mb)));
+        float scl;
+        const float pinv = inv;
+        row_scale(mrun, scl, inv);
+        values(list, mb, scl, pinv * scl, __any(vb < 0.0f));
+      }
+    }
+    // ---- O^T = S0 (r X)^T + acc.  r x enters as fp16 hi + lo: with fp16
+    // features the key dims are short, and an x rounded once to 11 bits cost
+    // up to 3e-4 of max|o| on 16-dim heads.
+    const float r = __builtin_amdgcn_exp2f(lw), ainv = p.scale * inv;
+    f16x8 xh[KB], xl[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      f16x4 h0, l0, h1 = {0, 0, 0, 0}, l1 = {0, 0, 0, 0};
+      split4(x[2 * kb], r, h0, l0);
+      if constexpr (NX > 1) split4(x[2 * kb + 1], r, h1, l1);
+      xh[kb] = cat(h0, h1);
+      xl[kb] = cat(l0, l1);
+    }
+    float* dst = outh + size_t(opaque(slot)) * Hv * DV + 4 * m;
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+      f32x4 d = z4;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const f16x8 a = *reinterpret_cast<const f16x8*>(s_plane + (16 * t + l16) * KP + 32 * kb + 8 * m);
+        d = mfma_h(a, xl[kb], d);
+        d = mfma_h(a, xh[kb], d);
+      }
+      const float4 si = *reinterpret_cast<const float4*>(s_inv + 16 * t + 4 * m);
+      const float4 o = make_float4(fmaf(d[0], si.x, acc[t][0] * ainv), fmaf(d[1], si.y, acc[t][1] * ainv),
+                                   fmaf(d[2], si.z, acc[t][2] * ainv), fmaf(d[3], si.w, acc[t][3] * ainv));
+      if (n < T) *reinterpret_cast<float4*>(dst + 16 * t) = n < nval ? o : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
 }
@@ -597,7 +928,7 @@ static int feat_cblocks(const LargeParams& p, int dk, int dv, int cpt) {
 }
 
 static dim3 feat_grid(const LargeParams& p, int dk, int dv, int cpt) {
-  return dim3(feat_cblocks(p, dk, dv, cpt) * ((p.T + kFP - 1) / kFP) * p.B);
+  return dim3(feat_cblocks(p, dk, dv, cpt) * ((p.T + kFP - 1) / kFP) * p.B + (p.ord ? p.B : 0));
 }
 
 template <int DK, int DV, typename TIn, bool FUSED>
@@ -658,7 +989,7 @@ static int large_dk(const VerifyArgs& a, const LargeParams& p, hipStream_t s) {
 
 // ws: the pull-back workspace (fp16 features, then the v~ scales) or, for
 // launch_features, the fp32 feature array
-static LargeParams large_params(const VerifyArgs& a, void* ws, bool half) {
+static LargeParams large_params(const VerifyArgs& a, void* ws, void* ord, bool half) {
   LargeParams p;
   p.B = a.B;
   p.T = a.T;
@@ -679,6 +1010,7 @@ static LargeParams large_params(const VerifyArgs& a, void* ws, bool half) {
   p.FH = half ? static_cast<_Float16*>(ws) : nullptr;
   p.Vs = half ? reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + fh_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv))
               : nullptr;
+  p.ord = static_cast<int16_t*>(ord);
   p.cp = CommitParams{};
   if (a.fused) {
     p.conv_state = a.conv_state_out;  // the features see the committed conv state
@@ -702,11 +1034,11 @@ static LargeParams large_params(const VerifyArgs& a, void* ws, bool half) {
   return p;
 }
 
-int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t stream) {
+int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, void* ord, hipStream_t stream) {
   if (a.T > kLMaxT) return set_error(GDN_EUNSUPPORTED, "verify: T=%d exceeds %d", a.T, kLMaxT);
   if (ws_bytes < large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv))
     return set_error(GDN_EINVAL, "verify: workspace of %zu bytes is too small", ws_bytes);
-  const LargeParams p = large_params(a, ws, true);
+  const LargeParams p = large_params(a, ws, ord, true);
   if (a.in_dtype == GDN_BF16) return large_dk<BF16>(a, p, stream);
   return large_dk<float>(a, p, stream);
 }
@@ -731,7 +1063,7 @@ static int launch_features_t(const VerifyArgs& a, const LargeParams& p, hipStrea
 
 int launch_features(const VerifyArgs& a, float* F, hipStream_t stream) {
   if (a.T > kLMaxT) return set_error(GDN_EUNSUPPORTED, "features: T=%d exceeds %d", a.T, kLMaxT);
-  const LargeParams p = large_params(a, F, false);
+  const LargeParams p = large_params(a, F, nullptr, false);
   if (a.in_dtype == GDN_BF16) return launch_features_t<BF16>(a, p, stream);
   return launch_features_t<float>(a, p, stream);
 }
@@ -746,10 +1078,14 @@ int launch_features(const VerifyArgs& a, float* F, hipStream_t stream) {
 // written before they are read, so nothing needs clearing.
 // ---------------------------------------------------------------------------
 static __device__ __align__(256) unsigned char scratch[GDN_NOALLOC_SCRATCH_BYTES];
+// the depth-first orders of the same problems: at least 129 nodes per tree of
+// at least 100 bytes (one key and one value head of 16)
+static __device__ __align__(256) unsigned char
+    order_scratch[size_t(GDN_NOALLOC_SCRATCH_BYTES) / ((kSmallMaxT + 1) * 100) * 3 * kLMaxT * sizeof(int16_t)];
 
-static void* scratch_address(int* rc) {
+static void* scratch_address(const void* symbol, int* rc) {
   static std::mutex mu;
-  static std::map<int, void*> addr;  // device -> address of its copy
+  static std::map<std::pair<const void*, int>, void*> addr;  // (array, device) -> address of its copy
   *rc = GDN_OK;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
@@ -757,15 +1093,15 @@ static void* scratch_address(int* rc) {
     return nullptr;
   }
   std::lock_guard<std::mutex> lock(mu);
-  auto it = addr.find(dev);
+  auto it = addr.find({symbol, dev});
   if (it != addr.end()) return it->second;
   void* ptr = nullptr;
-  const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
+  const hipError_t e = hipGetSymbolAddress(&ptr, symbol);
   if (e != hipSuccess || ptr == nullptr) {
     *rc = set_error(GDN_EHIP, "verify_noalloc: hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
     return nullptr;
   }
-  addr[dev] = ptr;
+  addr[{symbol, dev}] = ptr;
   return ptr;
 }
 
@@ -778,9 +1114,11 @@ int launch_verify_noalloc(const VerifyArgs& a, hipStream_t stream) {
                      "gdn_tree_verify, or split the batch)",
                      a.B, a.T, bytes, size_t(GDN_NOALLOC_SCRATCH_BYTES));
   int rc = GDN_OK;
-  void* ws = scratch_address(&rc);
+  void* ws = scratch_address(HIP_SYMBOL(scratch), &rc);
   if (!ws) return rc;
-  return launch_verify_large(a, ws, size_t(GDN_NOALLOC_SCRATCH_BYTES), stream);
+  void* ord = scratch_address(HIP_SYMBOL(order_scratch), &rc);
+  if (!ord) return rc;
+  return launch_verify_large(a, ws, size_t(GDN_NOALLOC_SCRATCH_BYTES), ord, stream);
 }
 
 // ---------------------------------------------------------------------------

@@ -185,15 +185,6 @@ __device__ __forceinline__ uint4 load_stream(const void* src) {
 // operand it reads alive across the barrier).
 __device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
 
-// The thread index as a value the compiler cannot see through: addresses
-// derived from it are computed where they are used instead of being hoisted
-// out of the head loop and held in registers across it (which spills, and a
-// spill reload waits for every vector memory operation issued before it).
-__device__ __forceinline__ int opaque(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
-
 // Value of v held by lane src of this wave (ds_bpermute).
 __device__ __forceinline__ float lane_gather(float v, int src) {
   return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));

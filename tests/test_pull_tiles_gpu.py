@@ -1,0 +1,80 @@
+"""GPU checks of the tiled pull-back (trees above 128 slots): tiles of 16 nodes
+in depth-first order, whose first node has just below, at and just above 16
+and 32 ancestors, and last tiles of 1, 15 and 16 nodes; against the CPU oracle
+with the bar of the other verify tests.  Values and keys that are not finite
+reach the nodes below them and no others."""
+import numpy as np
+import pytest
+
+from paper_2607_06763_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+O_TOL = 2e-3  # fp16 features and state plane, 11 significant bits (as in the other tests above 128 slots)
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2607_06763_amd import gdn_tree as G
+    G.lib()
+    return G
+
+
+def _broom(T, n, depth):
+    """A chain of `depth` nodes, the rest as leaves of its last node; slots
+    reversed so that the depth-first order is not the slot order."""
+    par = np.full(T, W.PAD, np.int32)
+    for i in range(n):
+        p = i - 1 if i <= depth else depth - 1
+        par[n - 1 - i] = W.ROOT if i == 0 else n - 1 - p
+    return par
+
+
+@pytest.mark.parametrize("T,n,depth", [
+    (129, 129, 15), (129, 129, 16), (145, 145, 17), (160, 159, 31), (160, 144, 32), (161, 161, 33),
+    (200, 1, 1), (192, 177, 100), (512, 511, 16), (512, 497, 300), (130, 130, 1),
+])
+def test_tile_edges(G, orc, T, n, depth):
+    import torch
+    par = np.stack([_broom(T, n, depth), W.random_tree(np.random.default_rng(T + n), T, n)])
+    w = W.make_random(9100 + T + depth, 2, T, 1, 2, 32, 64, "bf16", parent=par)
+    print(f"[gpu] tiles T={T} n={n} depth={depth}", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    ref = orc.verify(w)
+    err = np.max(np.abs(dt.out.cpu().numpy() - ref)) / np.max(np.abs(ref))
+    print(f"[gpu]   err {err:.3e}", flush=True)
+    assert err <= O_TOL
+
+
+@pytest.mark.parametrize("what,value", [("v", float("inf")), ("v", float("nan")), ("k", float("nan")), ("k", float("-inf"))])
+def test_not_finite_reaches_only_descendants(G, orc, what, value):
+    import torch
+    T = 200
+    w = W.make_random(9200, 2, T, 1, 2, 32, 32, "f32", shuffle=True)
+    ref = orc.prepare(w.parent)
+    b, j = 1, int(np.nonzero(w.parent[1] >= 0)[0][7])
+    print(f"[gpu] {what} = {value} at one node", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    clean = dt.out.clone().cpu().numpy()
+    x = getattr(dt, what).clone()
+    x[b, j, 0, 3] = value
+    setattr(dt, what, x)
+    dt.verify()
+    torch.cuda.synchronize()
+    got = dt.out.cpu().numpy()
+    desc = np.array([i == j or (int(ref["anc"][b, i, j // 64]) >> (j % 64)) & 1 for i in range(T)], bool)
+    heads = [0] if what == "v" else [0, 1]  # one value head, or both of the key head
+    keep = np.ones(got.shape[:3], bool)
+    for h in heads:
+        assert not np.isfinite(got[b, j, h]).all()
+        keep[b, desc, h] = False
+    np.testing.assert_array_equal(got[keep].view(np.int32), clean[keep].view(np.int32))
