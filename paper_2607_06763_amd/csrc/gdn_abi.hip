@@ -61,11 +61,12 @@ static int check_dims(const gdn_dims* d, const char* who) {
 // the feature workspace + gathered pull-back above.
 static int verify_any(const VerifyArgs& a, hipStream_t stream) {
   if (a.T <= kSmallMaxT) return launch_verify(a, stream);
-  const size_t bytes = (large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv) + 255) & ~size_t(255);
+  const size_t bytes =
+      large_order_offset(large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv)) + large_order_bytes(a.B);
   int rc = GDN_OK;
-  void* ws = stream_workspace(bytes + large_order_bytes(a.B), stream, &rc);
+  void* ws = stream_workspace(bytes, stream, &rc);
   if (!ws) return rc;
-  return launch_verify_large(a, ws, bytes, static_cast<unsigned char*>(ws) + bytes, stream);
+  return launch_verify_large(a, ws, bytes, stream);
 }
 
 }  // namespace gdn

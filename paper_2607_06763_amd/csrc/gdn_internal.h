@@ -356,9 +356,12 @@ int launch_verify(const VerifyArgs& a, hipStream_t stream);
 // trees of 129..512 slots: fp16 features into the workspace, then the
 // pull-back (the workspace holds large_workspace_bytes(...) bytes)
 size_t large_workspace_bytes(int B, int T, int Hk, int Hv, int dk, int dv);
-// the depth-first order of the trees, kept behind the features
-size_t large_order_bytes(int B);
-int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, void* ord, hipStream_t stream);
+// The depth-first order of the trees (three 16-bit arrays each) follows the
+// features at the next multiple of 256 bytes.
+inline size_t large_order_offset(size_t workspace_bytes) { return (workspace_bytes + 255) & ~size_t(255); }
+inline size_t large_order_bytes(int B) { return size_t(B) * 3 * GDN_MAX_T * sizeof(int16_t); }
+// ws: the features and the order
+int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 // A device buffer of at least bytes for work on stream, cached per (device,
 // stream) and grown on demand (never while the stream is being captured).
 void* stream_workspace(size_t bytes, hipStream_t stream, int* rc);

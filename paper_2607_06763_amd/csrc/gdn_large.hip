@@ -56,7 +56,7 @@ namespace gdn {
 
 constexpr int kLT = 512;      // threads of a pull-back workgroup (8 waves)
 constexpr int kLTile = 16;    // nodes per tile (one wave each)
-constexpr int kLMaxT = 512;   // tree slots supported
+constexpr int kLMaxT = GDN_MAX_T;  // tree slots supported
 constexpr int kFT = 256;      // threads of a feature workgroup
 
 struct LargeParams {
@@ -84,8 +84,6 @@ static size_t fh_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
 size_t large_workspace_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
   return fh_bytes(B, T, Hk, Hv, dk, dv) + size_t(B) * size_t(T) * size_t(Hv) * sizeof(float);
 }
-
-size_t large_order_bytes(int B) { return size_t(B) * 3 * kLMaxT * sizeof(int16_t); }
 
 size_t features_f32_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
   return size_t(B) * size_t(T) * size_t(2 * Hk * dk + Hv * dv) * sizeof(float);
@@ -1034,13 +1032,18 @@ static LargeParams large_params(const VerifyArgs& a, void* ws, void* ord, bool h
   return p;
 }
 
-int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, void* ord, hipStream_t stream) {
-  if (a.T > kLMaxT) return set_error(GDN_EUNSUPPORTED, "verify: T=%d exceeds %d", a.T, kLMaxT);
-  if (ws_bytes < large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv))
-    return set_error(GDN_EINVAL, "verify: workspace of %zu bytes is too small", ws_bytes);
+static int launch_large(const VerifyArgs& a, void* ws, void* ord, hipStream_t stream) {
   const LargeParams p = large_params(a, ws, ord, true);
   if (a.in_dtype == GDN_BF16) return large_dk<BF16>(a, p, stream);
   return large_dk<float>(a, p, stream);
+}
+
+int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t stream) {
+  if (a.T > kLMaxT) return set_error(GDN_EUNSUPPORTED, "verify: T=%d exceeds %d", a.T, kLMaxT);
+  const size_t order = large_order_offset(large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv));
+  if (ws_bytes < order + large_order_bytes(a.B))
+    return set_error(GDN_EINVAL, "verify: workspace of %zu bytes is too small", ws_bytes);
+  return launch_large(a, ws, static_cast<unsigned char*>(ws) + order, stream);
 }
 
 template <typename TIn>
@@ -1118,7 +1121,8 @@ int launch_verify_noalloc(const VerifyArgs& a, hipStream_t stream) {
   if (!ws) return rc;
   void* ord = scratch_address(HIP_SYMBOL(order_scratch), &rc);
   if (!ord) return rc;
-  return launch_verify_large(a, ws, size_t(GDN_NOALLOC_SCRATCH_BYTES), ord, stream);
+  if (a.T > kLMaxT) return set_error(GDN_EUNSUPPORTED, "verify: T=%d exceeds %d", a.T, kLMaxT);
+  return launch_large(a, ws, ord, stream);
 }
 
 // ---------------------------------------------------------------------------
