@@ -36,10 +36,13 @@
 // it, 4.4 GB per launch at 32 trees x 512 slots, 16 / 48 heads of 128, and
 // spent two thirds of its instructions on it.  A tile reads the union of its
 // nodes' paths, its own rows plus one chain, once.  That launch (with the
-// commit of the fused step) went from 503 to 363 us, verification alone at 16
-// x 250 slots, 16 / 32 heads, from 71 to 50 us.  128 registers and 80 KB keep
-// two workgroups on a CU: every variant with more spilled or ran one (the
-// values' accumulators live during the substitutions: 62 spills, 647 us).
+// commit of the fused step) went from 503 to 310 us, verification alone at 16
+// x 250 slots, 16 / 32 heads, from 71 to 48 us.  Of this, rows loaded whole
+// (RowStage) instead of one per lane are 363 -> 310 us at 512 slots.  128
+// registers and 80 KB keep two workgroups on a CU: every variant that spilled
+// more or ran one lost (the values' accumulators live during the
+// substitutions: 62 spills, 647 us).  Writing the outputs through LDS in whole
+// 256-byte runs changed nothing (B = 32) or lost 3 us (B = 1).
 // The fused decode step (Sec. 3.4.2) runs the conv-state shift of the
 // previous step's commit first, the features on the committed conv state,
 // and pull_kernel<..., FUSED>, which commits the previous accepted path into
@@ -509,41 +512,51 @@ __device__ __forceinline__ void ld_f(const float* src, float (&x)[N]) {
   }
 }
 
-// 16 rows of D halves as A operands in channel order: lane (l16, m) holds
-// channels 32 kb + 8 m .. + 7 of row l16 (zero beyond D = 16).
+// 16 rows of D halves on their way to LDS: a load covers whole rows (16 bytes
+// per lane, D / 8 lanes per row), which keeps the address lanes of the vector
+// cache few: with a row per lane a load took 64 lookups and the launch was
+// bound by them (32 x 512 slots: 295 us alone, 243 with whole rows).  In LDS row rho is at rho * 2 D bytes, its 32-byte granules
+// swizzled by rho.
 template <int D>
-struct RowFrag {
+struct RowStage {
   static constexpr int KB = D >= 32 ? D / 32 : 1;
-  static constexpr int kMask = D / 16 - 1;  // 32-byte granules of a row, swizzled by the row
-  f16x8 f[KB];
-  __device__ __forceinline__ void load(const _Float16* row, int m) {
+  static constexpr int kMask = D / 16 - 1;       // granule index mask
+  static constexpr int PPR = D / 8;              // 16-byte pieces per row
+  static constexpr int NI = (kLTile * PPR + 63) / 64;
+  f16x8 st[NI];
+  // rowoff: in lane rho (and rho + 16, ...), byte offset of row rho
+  __device__ __forceinline__ void load(const _Float16* base, int rowoff, int lane) {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      if constexpr (D >= 32) {
-        f[kb] = *reinterpret_cast<const f16x8*>(row + 32 * kb + 8 * m);
-      } else {
-        f[kb] = *reinterpret_cast<const f16x8*>(row + 8 * (m & 1));
-        if (m >= 2) f[kb] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      }
+    for (int i = 0; i < NI; ++i) {
+      const int rho = (64 / PPR * i + lane / PPR) & (kLTile - 1);
+      const int off = __builtin_amdgcn_ds_bpermute(4 * rho, rowoff) + 16 * (lane % PPR);
+      st[i] = *reinterpret_cast<const f16x8*>(reinterpret_cast<const char*>(base) + off);
     }
-  }
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) f[kb] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
   }
   // values that are not finite -> 0
   __device__ __forceinline__ void keep_finite() {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) f[kb][e] = fabsf((float)f[kb][e]) < 65536.0f ? f[kb][e] : (_Float16)0.0f;
+      for (int e = 0; e < 8; ++e) st[i][e] = fabsf((float)st[i][e]) < 65536.0f ? st[i][e] : (_Float16)0.0f;
   }
-  // -> LDS, row l16 at l16 * 2 D bytes
-  __device__ __forceinline__ void store(unsigned char* buf, int l16, int m) const {
+  __device__ __forceinline__ void store(unsigned char* buf, int lane) const {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-      if (D >= 32 || m < 2)
-        *reinterpret_cast<f16x8*>(buf + l16 * 2 * D + (((2 * kb + (m >> 1)) ^ l16) & kMask) * 32 + 16 * (m & 1)) = f[kb];
+    for (int i = 0; i < NI; ++i) {
+      const int rho = 64 / PPR * i + lane / PPR, pc = lane % PPR;
+      if (kLTile * PPR >= 64 || rho < kLTile)
+        *reinterpret_cast<f16x8*>(buf + rho * 2 * D + (((pc >> 1) ^ rho) & kMask) * 32 + 16 * (pc & 1)) = st[i];
+    }
+  }
+  // A operand in channel order: channels 32 kb + 8 m .. + 7 of row l16 (zero
+  // beyond D = 16)
+  __device__ static __forceinline__ unsigned char* piece(unsigned char* buf, int kb, int l16, int m) {
+    return buf + l16 * 2 * D + (((2 * kb + (m >> 1)) ^ l16) & kMask) * 32 + 16 * (m & 1);
+  }
+  __device__ static __forceinline__ f16x8 frag(unsigned char* buf, int kb, int l16, int m) {
+    f16x8 f = *reinterpret_cast<const f16x8*>(piece(buf, kb, l16, m));
+    if (D < 32 && m >= 2) f = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    return f;
   }
   // 4 channels 16 t + 4 m .. of row l16 (accumulator slot order)
   __device__ static __forceinline__ f16x4 slots(const unsigned char* buf, int t, int l16, int m) {
@@ -565,8 +578,8 @@ struct RowGate {
 template <int DK, int DV, typename TIn, bool FUSED>
 __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
   using SM = PullSmem<DK, DV>;
-  using KF = RowFrag<DK>;
-  using VF = RowFrag<DV>;
+  using KF = RowStage<DK>;
+  using VF = RowStage<DV>;
   constexpr int KP = SM::KP;
   constexpr int CK = DK / 16;                 // state columns per lane of the plane set-up
   constexpr int NX = DK / 16, NV = DV / 16;   // 16-channel tiles
@@ -603,29 +616,38 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
   const _Float16* Fk = Fb + nq + g * DK;
   const _Float16* Fv = Fb + 2 * nq + h * DV;
 
+  // ---- this thread's share of S0 (16 lanes per row), in flight first
+  constexpr int NR = (DV + kLT / 16 - 1) / (kLT / 16);  // rows per thread
+  float xs[FUSED ? 1 : NR][CK];
+  if constexpr (!FUSED) {
+    const float* S0 = p.S0 + (size_t(b) * Hv + h) * size_t(DV) * DK;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const int r = j * (kLT / 16) + (tid >> 4);
+      ld_f<CK>(S0 + size_t(r < DV ? r : DV - 1) * DK + (tid & 15) * CK, xs[j]);
+    }
+  }
   // ---- order and this head's gates by depth-first index
   const int16_t* ord = p.ord + size_t(b) * 3 * kLMaxT;
   for (int j = tid; j <= kLMaxT; j += kLT) {
     const bool real = j < nval;
     int row = nval > 0 ? ord[real ? j : nval - 1] : 0;  // past the nodes: the last one's row
-    RowGate g = {0.0f, 0.0f, 0.0f, 0};
+    const int end = ord[kLMaxT + (real ? j : 0)];
+    const bool live = j / kLTile * kLTile < nval;  // a tile with nodes
+    const int a = ord[2 * kLMaxT + (live ? j : 0)];
     row = row >= 0 && row < T ? row : 0;
+    RowGate g = {0.0f, 0.0f, 0.0f, 0};
     if (real) {
       const int nd = m_.order[bt + row];
+      g.vs = p.Vs[(bt + row) * Hv + h];
       const float la = __builtin_amdgcn_logf(ld(alpha, (bt + nd) * Hv + h));
       g.la = la < -512.0f ? -512.0f : la;  // a decay of 0 stays finite, 2^la is 0
       g.be = ld(beta, (bt + nd) * Hv + h);
-      // a key that is not finite (its row is NaN): beta NaN takes it to the nodes below
-      if (!(fabsf((float)Fk[size_t(row) * C]) < 65536.0f)) g.be = __builtin_nanf("");
-      g.vs = p.Vs[(bt + row) * Hv + h];
-      g.end = ord[kLMaxT + j];
+      g.end = end;
     }
     s_g[j] = g;
     s_row[j] = int16_t(row);
-    if (j < kLMaxT) {
-      const int a = j < ((nval + kLTile - 1) & ~(kLTile - 1)) ? ord[2 * kLMaxT + j] : kLMaxT;
-      s_path[j] = int16_t(a >= 0 && a < kLMaxT ? a : kLMaxT);
-    }
+    if (j < kLMaxT) s_path[j] = int16_t(a >= 0 && a < kLMaxT && live ? a : kLMaxT);
   }
   if constexpr (FUSED) {
     // ---- fused step: the previous step's accepted path is committed into
@@ -651,22 +673,20 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       if (tid % CS::LPR == 0) s_inv[r] = p.scale * inv;
     }
   } else if (nval > 0) {
-    // ---- S0 -> fp16 plane (16 lanes per row)
-    const float* S0 = p.S0 + (size_t(b) * Hv + h) * size_t(DV) * DK;
+    // ---- S0 -> fp16 plane
     const int ln = tid & 15;
-    for (int r0 = 0; r0 < DV; r0 += kLT / 16) {
-      const int r = r0 + (tid >> 4);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const int r = j * (kLT / 16) + (tid >> 4);
       if (r < DV) {  // uniform per 16-lane group
-        float xs[CK];
-        ld_f<CK>(S0 + size_t(r) * DK + ln * CK, xs);
         float mx = 0.0f;
 #pragma unroll
-        for (int e = 0; e < CK; ++e) mx = fmaxf(mx, fabsf(xs[e]));
+        for (int e = 0; e < CK; ++e) mx = fmaxf(mx, fabsf(xs[j][e]));
         mx = group_max<16>(mx);
         float sc, inv;
         row_scale(mx, sc, inv);
 #pragma unroll
-        for (int e = 0; e < CK; ++e) s_plane[r * KP + plane_col(ln * CK + e)] = (_Float16)(xs[e] * sc);
+        for (int e = 0; e < CK; ++e) s_plane[r * KP + plane_col(ln * CK + e)] = (_Float16)(xs[j][e] * sc);
         if (ln == 0) s_inv[r] = p.scale * inv;
       }
     }
@@ -703,44 +723,77 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // index of row tau of a chunk: the tile's own (lst null) or a list's
     auto index = [&](const int16_t* lst, int tau) { return lst ? int(lst[tau]) : n0 + tau; };
     const float y1 = one_f();
-    f16x8 qf[KB];  // q~ of column l16, channel order
+    // k~ and v~ rows of a chunk load one stage ahead: kf holds the next
+    // chunk's k~ while one is solved, vf the own v~ rows while the second is.
+    KF kf;
+    VF vf;
+    f16x8 qf[KB];   // q~ of column l16, channel order
+    f16x4 qc[NX];   // and accumulator order
     f32x4 x[NX], acc[NV];
+    const int16_t* path = s_path + n0;
+    const int near = path[kLTile - 1];  // parent of the tile's first node
+    auto row_off = [&](const int16_t* lst) {  // of operand row l16
+      return int(s_row[index(lst, tau_of(opaque(lane) & 15))]) * int(2 * C);
+    };
+    auto load_k = [&](const int16_t* lst) { kf.load(Fk, row_off(lst), opaque(lane)); };
+    auto load_v = [&](const int16_t* lst) { vf.load(Fv, row_off(lst), opaque(lane)); };
     {
-      const _Float16* q = Fb + size_t(s_row[n]) * C + g * DK;
-      KF t;
-      t.load(q, m);
+      KF qs;
+      qs.load(Fb + g * DK, int(s_row[n]) * int(2 * C), lane);
+      load_k(nullptr);
+      qs.store(buf, opaque(lane));
+      wave_lds_order();
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) qf[kb] = t.f[kb];
+      for (int kb = 0; kb < KB; ++kb) qf[kb] = KF::frag(buf, kb, l16, m);
 #pragma unroll
-      for (int t2 = 0; t2 < NX; ++t2) {
-        const f16x4 q4 = *reinterpret_cast<const f16x4*>(q + 16 * t2 + 4 * m);
-        x[t2] = f32x4{(float)q4[0], (float)q4[1], (float)q4[2], (float)q4[3]};
-      }
+      for (int t = 0; t < NX; ++t) qc[t] = KF::slots(buf, t, l16, m);
+      wave_lds_order();
     }
     float lw = 0.0f;  // log2 of the decay of the rows walked
     // The substitution over one chunk of path nodes: x and lw move up by the
     // chunk; returns the value coefficients r c / (v~ row scale) of the
-    // accumulator rows.  vmin: below 0 if a v~ row of this lane's is marked.
-    auto solve = [&](const int16_t* lst, float& vmin) -> f32x4 {
+    // accumulator rows.  kf: the chunk's k~ rows on entry; once they are in
+    // LDS, ahead() issues later loads.  vmin: below 0 if a v~ row of this
+    // lane's is marked.
+    auto solve = [&](const int16_t* lst, float& vmin, auto ahead) -> f32x4 {
       const bool own = lst == nullptr;
       const int ln = opaque(lane), l16 = ln & 15, m = ln >> 4;
       const int il = index(lst, tau_of(l16));
-      KF kf;
-      kf.load(Fk + size_t(s_row[il]) * C, m);
       const RowGate gl = s_g[il];
-      if (__any(gl.be != gl.be)) {
-        if (gl.be != gl.be) kf.zero();
-      }
       // ---- s = K x, Gram tile
       f32x4 s = z4, gm = z4;
+      kf.store(buf, ln);
+      ahead();
+      wave_lds_order();
+      f16x8 ka[KB];
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) gm = mfma_h(kf.f[kb], kf.f[kb], gm);
-      kf.store(buf, l16, m);
+      for (int kb = 0; kb < KB; ++kb) {
+        ka[kb] = KF::frag(buf, kb, l16, m);
+        gm = mfma_h(ka[kb], ka[kb], gm);
+      }
+      // a key that is not finite (its row is NaN) shows on the diagonal: a
+      // zero row then, and beta NaN takes it to the nodes below
+      uint32_t badk = 0;  // bit rho: operand row rho
+      {
+        const uint64_t w = __ballot((l16 >> 2) == m && !(fabsf(diag_entry(gm, l16)) < __builtin_inff()));
+        if (w) {  // uniform
+          badk = uint32_t((w | w >> 16 | w >> 32 | w >> 48) & 0xffffu);
+          gm = z4;
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) {
+            if ((badk >> l16) & 1) {
+              ka[kb] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+              if (DK >= 32 || m < 2) *reinterpret_cast<f16x8*>(KF::piece(buf, kb, l16, m)) = ka[kb];
+            }
+            gm = mfma_h(ka[kb], ka[kb], gm);
+          }
+          wave_lds_order();
+        }
+      }
       if (own) {
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) s = mfma_h(kf.f[kb], qf[kb], s);
+        for (int kb = 0; kb < KB; ++kb) s = mfma_h(ka[kb], qf[kb], s);
       }
-      wave_lds_order();
       if (!own) {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
@@ -770,7 +823,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       for (int e = 0; e < 4; ++e) {
         const RowGate g = ge[e];
         const bool on = ie[e] <= n && n < g.end;
-        bm[e] = on ? g.be : 0.0f;
+        bm[e] = on ? ((badk >> (4 * m + e)) & 1 ? __builtin_nanf("") : g.be) : 0.0f;
         la[e] = on ? g.la : 0.0f;
         vs[e] = fabsf(g.vs);
         vmin = fminf(vmin, g.vs);
@@ -792,6 +845,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
 #pragma unroll
       for (int t = 0; t < NX; ++t) {
         const f16x4 a = KF::columns(buf, t, l16, m);
+        if (own) x[t] = f32x4{(float)qc[t][0], (float)qc[t][1], (float)qc[t][2], (float)qc[t][3]};
         x[t] = mfma_h16(a, l0, x[t]);
         x[t] = mfma_h16(a, h0, x[t]);
       }
@@ -802,15 +856,14 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       return mm;
     };
     auto largest = [](f32x4 a) { return fmaxf(fmaxf(fabsf(a[0]), fabsf(a[1])), fmaxf(fabsf(a[2]), fabsf(a[3]))); };
-    // acc = f acc + V^T (scl mm) over the chunk
-    auto values = [&](const int16_t* lst, f32x4 mm, float scl, float f, bool marked) {
+    // acc = f acc + V^T (scl mm) over the chunk, whose v~ rows are in vf
+    auto values = [&](const int16_t* lst, f32x4 mm, float scl, float f, bool marked, auto ahead) {
       const int ln = opaque(lane), l16 = ln & 15, m = ln >> 4;
-      VF vf;
-      vf.load(Fv + size_t(s_row[index(lst, tau_of(l16))]) * C, m);
       f16x4 h0, l0;
       split4(mm, scl, h0, l0);
       if (marked) vf.keep_finite();
-      vf.store(buf, l16, m);
+      vf.store(buf, ln);
+      ahead();
       wave_lds_order();
 #pragma unroll
       for (int t = 0; t < NV; ++t) {
@@ -844,23 +897,30 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // The first two chunks' values follow both solutions: x and the solver's
     // registers are then not live together with acc (128 registers allow two
     // workgroups per CU).
-    const int16_t* path = s_path + n0;
-    const int near = path[kLTile - 1];  // parent of the tile's first node
-    float mrun, inv;              // largest value coefficient, power of two acc is divided by
+    float mrun, inv;  // largest value coefficient, power of two acc is divided by
+    auto none = [] {};
     {
       float va = 0.0f, vb = 0.0f;
-      const f32x4 ma = solve(nullptr, va);
+      const f32x4 ma = solve(nullptr, va, [&] {
+        if (near < kLMaxT) load_k(path);
+      });
       f32x4 mb = z4;
-      if (near < kLMaxT) mb = solve(path, vb);
+      if (near < kLMaxT)
+        mb = solve(path, vb, [&] { load_v(nullptr); });
+      else
+        load_v(nullptr);
       mrun = cross_max(fmaxf(largest(ma), largest(mb)));
       float scl;
       row_scale(mrun, scl, inv);
-      values(nullptr, ma, scl, 0.0f, __any(va < 0.0f));
-      if (near < kLMaxT) values(path, mb, scl, 1.0f, __any(vb < 0.0f));
+      values(nullptr, ma, scl, 0.0f, __any(va < 0.0f), [&] {
+        if (near < kLMaxT) load_v(path);
+      });
+      if (near < kLMaxT) values(path, mb, scl, 1.0f, __any(vb < 0.0f), none);
     }
-    if (path[0] < kLMaxT) {
-      // more than 16 ancestors: 16 at a time, found as the nodes before the
-      // tile whose subtree reaches past its first node
+    if (path[0] < kLMaxT && path[0] > 0) {
+      // more than 16 ancestors (the 16th is not the root): 16 at a time,
+      // found as the nodes before the tile whose subtree reaches past its
+      // first node
       const int np = m_.pdep[bt + s_row[n0]];
       for (int base = np - 2 * kLTile; base > -kLTile; base -= kLTile) {
         if (lane < kLTile) list[lane] = int16_t(kLMaxT);
@@ -872,13 +932,15 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
           }
         }
         wave_lds_order();
+        load_k(list);
         float vb = 0.0f;
-        const f32x4 mb = solve(list, vb);
+        const f32x4 mb = solve(list, vb, none);
+        load_v(list);  // not ahead: acc is live here
         mrun = fmaxf(mrun, cross_max(largest(mb)));
         float scl;
         const float pinv = inv;
         row_scale(mrun, scl, inv);
-        values(list, mb, scl, pinv * scl, __any(vb < 0.0f));
+        values(list, mb, scl, pinv * scl, __any(vb < 0.0f), none);
       }
     }
     // ---- O^T = S0 (r X)^T + acc.  r x enters as fp16 hi + lo: with fp16
