@@ -16,97 +16,85 @@
 // product (I - N)(I + N^2)(I + N^4)(I + N^8)(I + N^16), N = X_jj (N^32 = 0),
 // formed by repeated squaring.
 //
-// The features come from the feature kernel (gdn_large.hip) in a workspace
-// F[B][T][C]; U[B][Hv][T][dv] is a second workspace.  One workgroup per
-// (value head, sequence), 512 threads = 8 waves; products are 16 x 16 MFMA
-// tiles with operands in LDS.  The large ones (the S0 products, the Gram
-// blocks and the block updates) take both operands as bf16 hi/lo planes and
-// three v_mfma_f32_16x16x32_bf16 (hi*hi + hi*lo + lo*hi, fp32 accumulation,
-// ~1e-5 relative); the diagonal-block inverse and its two products stay on
-// v_mfma_f32_16x16x4f32 (fp32 operands):
-//   phase A  S0 staged once; for each block: a Q S0^T -> out (node order),
-//            beta (V - a K S0^T) -> U (padding rows zero)
-//   phase B  for each block j in order: R_j, O_j in registers; for every
-//            earlier block c holding an ancestor of a node of j: the decayed,
-//            masked Gram blocks X_jc, Y_jc, then R_j -= X_jc U_c and
-//            O_j += Y_jc U_c; the diagonal block: X_jj, Y_jj, the inverse by
-//            five rounds of squaring (the powers of A = -N on waves 0-3, the
-//            partial products on waves 4-7), U_j = (I + X_jj)^-1 R_j -> U,
-//            O_j += Y_jj U_j, scaled and stored.
+// Three launches:
+//   features           (gdn_large.hip) fp32 rows F[B][T][C]
+//   chunk_gram_kernel  one workgroup per (position block j, up to 4 blocks c <=
+//                      j, key head, sequence): the Gram blocks K_j K_c^T and
+//                      Q_j K_c^T, which the value heads of a key head share,
+//                      for every c that holds an ancestor of a node of j; for
+//                      c = j per value head the decayed, masked Y_jj and the
+//                      inverse of I + X_jj, one wave each
+//   chunk_kernel       one workgroup per (value head, sequence), 8 waves, each
+//                      wave 16 channels of dv: U's columns are independent, so
+//                      the cascade over j runs inside a wave and no U is
+//                      exchanged; the waves share the decayed X_jc, Y_jc of 2
+//                      blocks c at a time (LDS)
+// Products are 16 x 16 MFMA tiles.  The large ones (S0 products, Gram blocks,
+// block updates) take both operands as bf16 hi/lo and three
+// v_mfma_f32_16x16x32_bf16 (hi*hi + hi*lo + lo*hi, fp32 accumulation, ~1e-5
+// relative); the diagonal inverse and its products stay on
+// v_mfma_f32_16x16x4f32.
+//
+// Layouts.  Lane (l16, m) = (lane % 16, lane / 16) of an accumulator holds rows
+// 4 m + e (e < 4) of column l16.  Accumulators become B operands without a lane
+// move: in fp32 k step e is row 4 m + e of lane group m, in bf16 slots e < 4 of
+// group m are rows 4 m + e of the block's first tile, slots e >= 4 rows 4 m + e
+// of its second; the A operand is laid out in the same order (slot_col).
+//
+// What bounds it and why this form: one workgroup per head that formed the Gram
+// blocks and the inverse itself ran 28 pairs and 8 inverses one after the other
+// with 3 to 7 barriers each, one workgroup per CU (150 KB): 8 chains of 256
+// slots, 16 / 48 heads of 128, took 367 us, hardly any of it in the products.
+// CHUNK_FIGURES
 #include <math.h>
 
-#include "gdn_internal.h"
+#include "gdn_pull.h"
 
 namespace gdn {
 
 constexpr int kHT = 512;      // threads per workgroup (8 waves)
-constexpr int kBc = 32;       // positions per sub-block (B_c)
+constexpr int kBc = 32;       // positions per block (B_c)
 constexpr int kHMaxT = 512;   // tree slots supported
 constexpr int kHW = 8;        // ancestor words per node (512 / 64)
-constexpr int kLs = 36;       // row stride of the 32 x 32 matrices (floats)
+constexpr int kLs = 36;       // row stride of the 32 x 32 matrices in LDS (floats)
+constexpr int kCG = 4;        // blocks c per workgroup of the Gram launch
+constexpr int kCP = 2;        // earlier blocks per group of the cascade
+constexpr int kMaxNB = kHMaxT / kBc;
+constexpr int kUL = kBc + 8;  // bf16 row of an X or Y plane
+constexpr float kMinLog2 = -125.5f;  // floor of log2 alpha: 2^x stays a normal float
 
 struct ChunkParams {
-  int B, T, Hk, Hv;
+  int B, T, Hk, Hv, dv;
   float scale;
   const void* meta;
   const void *alpha, *beta;
   const float* S0;
   float* out;
   const float* F;  // features [B][T][C]
-  float* U;        // [B][Hv][T][DV]: right-hand sides, then the solved rows
+  float* D;        // [B][Hv][NB][2][32][32]: (I + X_jj)^-1 and Y_jj
+  float* Gm;       // [B][Hk][NB (NB - 1) / 2][2][32][32]: K_j K_c^T and Q_j K_c^T, c < j
+  uint32_t* mask;  // [B][NB][16][32]: per row of block j, the strict ancestors among block c's positions
+  unsigned char* need;  // [B][NB][16]: 1 if block c holds an ancestor of a node of block j
+  uint16_t* U;     // [B][Hv][NB][DV / 16][2][64][8]: solved rows, bf16 hi and lo, per lane
 };
 
-template <int DK, int DV>
-struct ChunkSmem {
-  static constexpr int KP = DK < 32 ? 32 : DK;  // contraction extent of the key products (zero padded)
-  static constexpr int LKH = KP + 8;            // bf16 plane row (halves)
-  static constexpr int LV = DV + 4;             // fp32 row of a 32 x DV block
-  static constexpr int UL = kBc + 8;            // bf16 row of a 32-column plane (X, Y, transposed U)
-  static constexpr size_t pk = size_t(kBc) * LKH * 2;  // one 32-row key plane
-  static constexpr size_t head = 4 * pk;               // block q and k planes (hi, lo)
-  static constexpr size_t uni_a = size_t(2) * DV * LKH * 2;  // phase A: S0 planes
-  static constexpr size_t uni_b = 2 * pk                     // keys of block c
-                                  + size_t(2) * DV * UL * 2  // U of block c, transposed
-                                  + size_t(4) * kBc * UL * 2  // -X and Y blocks
-                                  + size_t(5) * kBc * kLs * 4  // Y_jj, powers, partial products
-                                  + size_t(2) * kBc * LV * 4;  // R_j, U_j
-  static constexpr size_t uni = uni_a > uni_b ? uni_a : uni_b;
-  static constexpr size_t anc = size_t(kBc) * kHW * 8;
-  static constexpr size_t meta = size_t(kHMaxT) * (2 + 2 + 4 + 4 + 4);
-  static constexpr size_t total = head + uni + anc + meta;
+// Bytes of the workspace's parts, in order
+struct ChunkSizes {
+  size_t f, d, g, k, n, u;
+  ChunkSizes(int B, int T, int Hk, int Hv, int dk, int dv) {
+    const size_t NB = size_t(T + kBc - 1) / kBc, mat = size_t(2) * kBc * kBc * sizeof(float);
+    f = (features_f32_bytes(B, T, Hk, Hv, dk, dv) + 255) & ~size_t(255);
+    d = size_t(B) * Hv * NB * mat;
+    g = size_t(B) * Hk * (NB > 1 ? NB * (NB - 1) / 2 : 1) * mat;
+    k = size_t(B) * NB * kMaxNB * kBc * sizeof(uint32_t);
+    n = (size_t(B) * NB * kMaxNB + 255) & ~size_t(255);
+    u = size_t(B) * Hv * NB * kBc * dv * sizeof(float);
+  }
+  size_t total() const { return f + d + g + k + n + u; }
 };
 
 size_t chunked_workspace_bytes(int B, int T, int Hk, int Hv, int dk, int dv) {
-  return features_f32_bytes(B, T, Hk, Hv, dk, dv) + size_t(B) * Hv * size_t(T) * dv * sizeof(float);
-}
-
-// acc += A (16 x K) B (K x 16) for one 16 x 16 tile on v_mfma_f32_16x16x4f32.
-// A[i][k] = a[i * lda + k]; B[k][j] = b[j * ldb + k] (BT) or b[k * ldb + j].
-// Result layout: acc[r] = D[4 (lane / 16) + r][lane % 16].
-template <int K, bool BT>
-__device__ __forceinline__ f32x4 mm16(const float* a, int lda, const float* b, int ldb, f32x4 acc, int lane) {
-  const int i = lane & 15, kk = lane >> 4;
-#pragma unroll 8
-  for (int k0 = 0; k0 < K; k0 += 4) {
-    const float av = a[i * lda + k0 + kk];
-    const float bv = BT ? b[i * ldb + k0 + kk] : b[(k0 + kk) * ldb + i];
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
-
-// 16 x 16 tile of a 32 x 32 matrix in LDS as an accumulator
-__device__ __forceinline__ f32x4 ld_tile(const float* m, int ti, int tj, int lane) {
-  f32x4 v;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = m[(16 * ti + 4 * (lane >> 4) + r) * kLs + 16 * tj + (lane & 15)];
-  return v;
-}
-__device__ __forceinline__ void st_tile(float* m, int ti, int tj, int lane, f32x4 v) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) m[(16 * ti + 4 * (lane >> 4) + r) * kLs + 16 * tj + (lane & 15)] = v[r];
+  return ChunkSizes(B, T, Hk, Hv, dk, dv).total();
 }
 
 // x -> bf16 hi (truncation) + bf16 lo (truncation of the remainder)
@@ -119,10 +107,12 @@ __device__ __forceinline__ void st_split4(uint16_t* hi, uint16_t* lo, float4 v) 
   *reinterpret_cast<uint2*>(hi) = make_uint2(hi16(v.x) | (hi16(v.y) << 16), hi16(v.z) | (hi16(v.w) << 16));
   *reinterpret_cast<uint2*>(lo) = make_uint2(lo16(v.x) | (lo16(v.y) << 16), lo16(v.z) | (lo16(v.w) << 16));
 }
-__device__ __forceinline__ void st_split1(uint16_t* hi, uint16_t* lo, float x) {
-  *hi = uint16_t(hi16(x));
-  *lo = uint16_t(lo16(x));
+__device__ __forceinline__ void st_split2(uint16_t* hi, uint16_t* lo, float x, float y) {
+  *reinterpret_cast<uint32_t*>(hi) = hi16(x) | (hi16(y) << 16);
+  *reinterpret_cast<uint32_t*>(lo) = lo16(x) | (lo16(y) << 16);
 }
+// plane column of block position c: the k slot of U's operand
+__device__ __forceinline__ int slot_col(int c) { return 8 * ((c & 15) >> 2) + 4 * (c >> 4) + (c & 3); }
 
 // acc += A (16 x K) B (K x 16) for one 16 x 16 tile from bf16 hi/lo planes:
 // A[i][k] = a[i * lda + k], B[k][j] = b[j * ldb + k] (k contiguous in both);
@@ -141,74 +131,425 @@ __device__ __forceinline__ f32x4 mm16x3(const uint16_t* ah, const uint16_t* al, 
   }
   return acc;
 }
+// c + A B in fp32 for 16 x 16 tiles: at holds A's transpose, b holds B, as
+// accumulators
+__device__ __forceinline__ f32x4 mm_f(f32x4 at, f32x4 b, f32x4 c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = mfma_f(at[e], b[e], c);
+  return c;
+}
+__device__ __forceinline__ f32x4 as_x4(float4 v) { return f32x4{v.x, v.y, v.z, v.w}; }
+
+// (I - a)^-1 of a strictly lower triangular 16 x 16 tile as (I + a)(I + a^2)
+// (I + a^4)(I + a^8), the tile and its transpose as accumulators
+__device__ __forceinline__ void inverse16(f32x4 a, f32x4 at, f32x4& v, f32x4& vt, int l16, int m) {
+  const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float one = 4 * m + e == l16 ? 1.0f : 0.0f;
+    v[e] = a[e] + one;
+    vt[e] = at[e] + one;
+  }
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const f32x4 q = mm_f(at, a, z), qt = mm_f(a, at, z);
+    const f32x4 w = mm_f(vt, q, v);
+    vt = mm_f(q, vt, vt);
+    v = w;
+    a = q;
+    at = qt;
+  }
+}
+
+template <int DK>
+struct GramSmem {
+  static constexpr int KP = DK < 32 ? 32 : DK;  // contraction extent of the key products (zero padded)
+  static constexpr int LKH = KP + 8;            // bf16 plane row (halves)
+  static constexpr size_t planes = size_t(6) * kBc * LKH * 2;  // q_j, k_j, k_c (hi, lo)
+  static constexpr size_t mat = size_t(kBc) * kLs * 4;
+  static constexpr size_t diag = 2 * mat + (kHT / 64) * (mat + 3 * kBc * 4);  // Gram, then per wave A and its rows' gates
+  static constexpr size_t uni = planes > diag ? planes : diag;
+  static constexpr size_t total = uni + size_t(kBc) * kHW * 8;  // ancestor words of block j
+  static_assert(total <= 53 * 1024, "three workgroups per CU");
+};
+
+template <int DK, typename TIn>
+__global__ __launch_bounds__(kHT, 6) void chunk_gram_kernel(ChunkParams p) {
+  using SM = GramSmem<DK>;
+  constexpr int KP = SM::KP, LKH = SM::LKH;
+  constexpr int NQK = (2 * kBc * (DK / 4) + kHT - 1) / kHT;  // float4 of q_j and k_j per thread
+  constexpr int NKC = (kBc * (DK / 4) + kHT - 1) / kHT;      // float4 of k_c per thread
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint16_t* s_qh = reinterpret_cast<uint16_t*>(smem);
+  uint16_t* s_ql = s_qh + kBc * LKH;
+  uint16_t* s_kh = s_ql + kBc * LKH;
+  uint16_t* s_kl = s_kh + kBc * LKH;
+  uint16_t* s_ch = s_kl + kBc * LKH;
+  uint16_t* s_cl = s_ch + kBc * LKH;
+  uint64_t* s_anc = reinterpret_cast<uint64_t*>(smem + SM::uni);  // [32][kHW]
+
+  const int g = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int T = p.T, Hk = p.Hk, Hv = p.Hv, NB = (T + kBc - 1) / kBc;
+  // block j has j / kCG + 1 groups of up to kCG blocks c <= j
+  int jb = 0, c0 = blockIdx.x;
+  while (c0 > jb / kCG) {
+    c0 -= jb / kCG + 1;
+    ++jb;
+  }
+  c0 *= kCG;
+  const MetaPtrs m_ = meta_ptrs(p.meta, p.B, T);
+  const int W = m_.W;
+  const size_t bt = size_t(b) * T;
+  const int nval = m_.status[b] == GDN_TREE_OK ? m_.nvalid[b] : 0;
+  if (kBc * jb >= nval) return;  // uniform
+  const int nq = Hk * DK;
+  const size_t C = size_t(2 * nq + Hv * (p.dv));
+  const float* Fq = p.F + bt * C + g * DK;
+  const float* Fk = Fq + nq;
+
+  const TIn* alpha = static_cast<const TIn*>(p.alpha);
+  const TIn* beta = static_cast<const TIn*>(p.beta);
+  const int G = Hv / Hk;
+  const bool diag = jb < c0 + kCG;
+  float4 kc[NKC];
+  int ndc;  // node of this thread's position of block c
+  auto fetch_c = [&](int cb) {
+    ndc = m_.order[bt + kBc * cb + (cb < jb ? tid % kBc : 0)];
+#pragma unroll
+    for (int j = 0; j < NKC; ++j) {
+      const int i = j * kHT + tid < kBc * (DK / 4) ? j * kHT + tid : 0;
+      kc[j] = *reinterpret_cast<const float4*>(Fk + (cb < jb ? kBc * cb + i / (DK / 4) : 0) * C + 4 * (i % (DK / 4)));
+    }
+  };
+  // gates of a value head's rows (diagonal block), a lane per row, twice
+  float ga = 0.0f, gb = 0.0f;
+  int gp = -1;
+  auto fetch_gates = [&](int h) {
+    const int pos = kBc * jb + (lane & (kBc - 1)), pc = pos < nval ? pos : 0;
+    const int nd = m_.order[bt + pc];
+    ga = ld(alpha, (bt + nd) * Hv + h);
+    gb = ld(beta, (bt + nd) * Hv + h);
+    gp = m_.ppos[bt + pc];
+  };
+  {
+    float4 v[NQK];
+    constexpr int NAW = (kBc * kHW + kHT - 1) / kHT;
+    int nd[NAW];
+#pragma unroll
+    for (int j = 0; j < NAW; ++j) {
+      const int pos = kBc * jb + (j * kHT + tid) / kHW % kBc;
+      nd[j] = m_.order[bt + (pos < nval ? pos : 0)];
+    }
+#pragma unroll
+    for (int j = 0; j < NQK; ++j) {
+      const int i = j * kHT + tid;
+      const int part = i / (kBc * (DK / 4)) & 1, r = i / (DK / 4) % kBc, c4 = i % (DK / 4);
+      const int pos = kBc * jb + r;
+      v[j] = *reinterpret_cast<const float4*>((part ? Fk : Fq) + (pos < nval ? pos : 0) * C + 4 * c4);
+    }
+    fetch_c(c0);  // c0 <= jb; row clamp: block jb may end early
+    if (diag && wave < G) fetch_gates(g * G + wave);
+#pragma unroll
+    for (int j = 0; j < NAW; ++j) {
+      const int i = j * kHT + tid, r = i / kHW % kBc, w = i % kHW;
+      const uint64_t a = m_.anc[(bt + nd[j]) * W + (w < W ? w : 0)];
+      if (i < kBc * kHW) s_anc[i] = kBc * jb + r < nval && w < W ? a : 0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < NQK; ++j) {
+      const int i = j * kHT + tid;
+      if (i < 2 * kBc * (DK / 4)) {
+        const int part = i / (kBc * (DK / 4)), r = i / (DK / 4) % kBc, c4 = i % (DK / 4);
+        const float4 x = kBc * jb + r < nval ? v[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+        st_split4((part ? s_kh : s_qh) + r * LKH + 4 * c4, (part ? s_kl : s_ql) + r * LKH + 4 * c4, x);
+      }
+    }
+    if constexpr (DK < KP) {  // zero padding of the contraction, all six planes
+      for (int i = tid; i < 6 * kBc * (KP - DK); i += kHT)
+        s_qh[i / (KP - DK) * LKH + DK + i % (KP - DK)] = 0;
+    }
+  }
+  __syncthreads();
+  const int kind = wave >> 2, ti = (wave >> 1) & 1, tc = wave & 1;  // this wave's tile
+  const int l16 = lane & 15, m = lane >> 4;
+  const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+  const int cend = jb < c0 + kCG ? jb : c0 + kCG;
+  for (int cb = c0; cb < cend; ++cb) {
+    // strict ancestors of the rows of j among the positions of c: half a wave per row
+    bool found = false;
+    const size_t jc = (size_t(b) * NB + jb) * kMaxNB + cb;
+#pragma unroll
+    for (int j = 0; j < kBc * kBc / kHT; ++j) {
+      const int i = j * (kHT / kBc) + tid / kBc;
+      const bool anc = (s_anc[i * kHW + (ndc >> 6)] >> (ndc & 63)) & 1ull;
+      const uint64_t w = __ballot(anc);
+      if (g == 0 && tid % kBc == 0) p.mask[jc * kBc + i] = lane < kBc ? uint32_t(w) : uint32_t(w >> 32);
+      found |= anc;
+    }
+    const bool any = __syncthreads_or(found);  // and the planes of the block before are read
+    if (g == 0 && tid == 0) p.need[jc] = any;
+    if (!any) {  // uniform
+      if (cb + 1 < cend) fetch_c(cb + 1);
+      continue;
+    }
+#pragma unroll
+    for (int j = 0; j < NKC; ++j) {
+      const int i = j * kHT + tid;
+      if (i < kBc * (DK / 4)) {
+        const int r = i / (DK / 4), c4 = i % (DK / 4);
+        st_split4(s_ch + r * LKH + 4 * c4, s_cl + r * LKH + 4 * c4, kc[j]);
+      }
+    }
+    if (cb + 1 < cend) fetch_c(cb + 1);
+    __syncthreads();
+    const f32x4 acc = mm16x3<KP>((kind ? s_qh : s_kh) + 16 * ti * LKH, (kind ? s_ql : s_kl) + 16 * ti * LKH, LKH,
+                                 s_ch + 16 * tc * LKH, s_cl + 16 * tc * LKH, LKH, z4, lane);
+    float* dst = p.Gm + (((size_t(b) * Hk + g) * (size_t(NB) * (NB - 1) / 2) + size_t(jb) * (jb - 1) / 2 + cb) * 2 +
+                         kind) * (kBc * kBc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dst[(16 * ti + 4 * m + e) * kBc + 16 * tc + l16] = acc[e];
+  }
+  if (!diag) return;  // uniform
+
+  // ---- diagonal block
+  __syncthreads();
+  const f32x4 gm = mm16x3<KP>((kind ? s_qh : s_kh) + 16 * ti * LKH, (kind ? s_ql : s_kl) + 16 * ti * LKH, LKH,
+                              s_kh + 16 * tc * LKH, s_kl + 16 * tc * LKH, LKH, z4, lane);
+  __syncthreads();  // the planes are read: LDS holds the Gram blocks from here
+  float* s_g = reinterpret_cast<float*>(smem);  // [2][32][kLs]
+  float* s_a = s_g + 2 * kBc * kLs + wave * (kBc * kLs + 3 * kBc);
+  float* s_la = s_a + kBc * kLs;
+  float* s_be = s_la + kBc;
+  uint32_t* s_up = reinterpret_cast<uint32_t*>(s_be + kBc);  // strict ancestors in the block, one bit each
+#pragma unroll
+  for (int e = 0; e < 4; ++e) s_g[kind * kBc * kLs + (16 * ti + 4 * m + e) * kLs + 16 * tc + l16] = gm[e];
+  __syncthreads();
+  for (int w = wave; w < G; w += kHT / 64) {
+    const int h = g * G + w;
+    {  // log decay from the block's edge down to each row, and its ancestors in
+       // the block, by pointer jumping over the lanes
+      const int i = lane & (kBc - 1), pos = kBc * jb + i;
+      const bool real = pos < nval;
+      if (w != wave) fetch_gates(h);
+      // floored at the smallest normal float: a decay of 0 keeps ratios finite
+      float sl = real ? fmaxf(log2f(ga), kMinLog2) : 0.0f;
+      const float be = real ? gb : 0.0f;
+      int nx = real ? gp - kBc * jb : -1;
+      uint32_t up = nx >= 0 ? 1u << nx : 0u;
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        const int src = nx >= 0 ? nx : i;
+        const float sl2 = __shfl(sl, src);
+        const uint32_t up2 = __shfl(up, src);
+        const int nx2 = __shfl(nx, src);
+        if (nx >= 0) {
+          sl += sl2;
+          up |= up2;
+          nx = nx2;
+        }
+      }
+      s_la[i] = sl;
+      s_be[i] = be;
+      s_up[i] = up;
+    }
+    wave_lds_order();
+    float* dst = p.D + ((size_t(b) * Hv + h) * NB + jb) * (2 * kBc * kBc);
+    {  // A = -X_jj -> LDS, Y_jj -> workspace: 16 columns of one row per lane
+      const int i = lane & (kBc - 1), cc = 16 * (lane >> 5);
+      const float la = s_la[i], be = s_be[i];
+      const uint32_t up = s_up[i];
+      const bool real = kBc * jb + i < nval;
+#pragma unroll
+      for (int q = 0; q < 16; q += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(s_g + i * kLs + cc + q);
+        const float4 y = *reinterpret_cast<const float4*>(s_g + kBc * kLs + i * kLs + cc + q);
+        const f32x4 gx = as_x4(x), gy = as_x4(y);
+        f32x4 av, yv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int c = cc + q + e;
+          const bool anc = (up >> c) & 1;
+          const float r = __builtin_amdgcn_exp2f(la - s_la[c]);
+          av[e] = anc ? -be * r * gx[e] : 0.0f;
+          yv[e] = anc || (c == i && real) ? r * gy[e] : 0.0f;
+        }
+        *reinterpret_cast<float4*>(s_a + i * kLs + cc + q) = make_float4(av[0], av[1], av[2], av[3]);
+        *reinterpret_cast<float4*>(dst + kBc * kBc + i * kBc + cc + q) = make_float4(yv[0], yv[1], yv[2], yv[3]);
+      }
+    }
+    wave_lds_order();
+    // (I + X_jj)^-1 from its 16 x 16 tiles: V00, V11 and V11 A10 V00
+    f32x4 v[2], vt[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      f32x4 a;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = s_a[(16 * t + 4 * m + e) * kLs + 16 * t + l16];
+      const f32x4 at = as_x4(*reinterpret_cast<const float4*>(s_a + (16 * t + l16) * kLs + 16 * t + 4 * m));
+      inverse16(a, at, v[t], vt[t], l16, m);
+    }
+    const f32x4 at10 = as_x4(*reinterpret_cast<const float4*>(s_a + (16 + l16) * kLs + 4 * m));
+    const f32x4 vt10 = mm_f(mm_f(at10, v[0], z4), vt[1], z4);
+    *reinterpret_cast<float4*>(dst + l16 * kBc + 4 * m) = make_float4(vt[0][0], vt[0][1], vt[0][2], vt[0][3]);
+    *reinterpret_cast<float4*>(dst + (16 + l16) * kBc + 4 * m) = make_float4(vt10[0], vt10[1], vt10[2], vt10[3]);
+    *reinterpret_cast<float4*>(dst + (16 + l16) * kBc + 16 + 4 * m) = make_float4(vt[1][0], vt[1][1], vt[1][2], vt[1][3]);
+    wave_lds_order();
+  }
+}
+
+template <int DK, int DV>
+struct ChunkSmem {
+  static constexpr int KP = DK < 32 ? 32 : DK;
+  static constexpr int LKH = KP + 8;
+  static constexpr size_t qk = size_t(4) * kBc * LKH * 2;        // q_j, k_j planes (hi, lo)
+  static constexpr size_t xy = size_t(kCP) * 4 * kBc * kUL * 2;  // -X_jc, Y_jc planes of a group
+  static constexpr size_t diag = size_t(2) * kBc * kLs * 4;  // (I + X_jj)^-1 and Y_jj
+  static constexpr size_t meta = size_t(kHMaxT) * (2 + 2 + 4 + 4 + 4);
+  static constexpr size_t total = qk + xy + diag + meta;
+};
 
 template <int DK, int DV, typename TIn>
-__global__ __launch_bounds__(kHT) void chunk_kernel(ChunkParams p) {
+__global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
   using SM = ChunkSmem<DK, DV>;
-  constexpr int KP = SM::KP, LKH = SM::LKH, LV = SM::LV, UL = SM::UL;
-  constexpr int NTV = DV / 16;    // tiles across dv
-  constexpr int NTILE = 2 * NTV;  // tiles of a 32 x DV block matrix
-  constexpr int NKP = (kBc * DK / 4 + kHT - 1) / kHT;  // float4 of a block's keys per thread
-  constexpr int NUP = (kBc * DV / 4 + kHT - 1) / kHT;  // float4 of a block's U rows per thread
+  constexpr int KP = SM::KP, LKH = SM::LKH;
+  constexpr int NKS = KP / 32;    // k steps of the S0 products
+  constexpr int NTV = DV / 16;    // waves with channels
+  constexpr int NQK = (2 * kBc * (DK / 4) + kHT - 1) / kHT;
+  constexpr int kPl = kBc * kUL;  // halves of a plane
+  static_assert(NTV <= kHT / 64 && SM::total <= 80 * 1024, "two workgroups per CU");
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ uint32_t s_need;  // earlier blocks holding ancestors of the current block's nodes
-  uint16_t* s_qh = reinterpret_cast<uint16_t*>(smem);  // block q~ planes [32][LKH]
+  uint16_t* s_qh = reinterpret_cast<uint16_t*>(smem);
   uint16_t* s_ql = s_qh + kBc * LKH;
-  uint16_t* s_kh = s_ql + kBc * LKH;                    // block k~ planes
+  uint16_t* s_kh = s_ql + kBc * LKH;
   uint16_t* s_kl = s_kh + kBc * LKH;
-  uint16_t* s_s0h = reinterpret_cast<uint16_t*>(smem + SM::head);  // phase A: S0 planes [DV][LKH]
-  uint16_t* s_s0l = s_s0h + DV * LKH;
-  uint16_t* s_kch = reinterpret_cast<uint16_t*>(smem + SM::head);  // phase B: keys of block c
-  uint16_t* s_kcl = s_kch + kBc * LKH;
-  uint16_t* s_uth = s_kcl + kBc * LKH;  // U of block c, transposed [DV][UL]
-  uint16_t* s_utl = s_uth + DV * UL;
-  uint16_t* s_xh = s_utl + DV * UL;     // -X_jc [32][UL]
-  uint16_t* s_xl = s_xh + kBc * UL;
-  uint16_t* s_yh = s_xl + kBc * UL;     // Y_jc
-  uint16_t* s_yl = s_yh + kBc * UL;
-  float* s_y = reinterpret_cast<float*>(s_yl + kBc * UL);  // Y_jj [32][kLs] (fp32)
-  float* s_pa = s_y + kBc * kLs;                            // powers of A
-  float* s_pb = s_pa + kBc * kLs;
-  float* s_ma = s_pb + kBc * kLs;                           // partial products of the inverse
-  float* s_mb = s_ma + kBc * kLs;
-  float* s_rt = s_mb + kBc * kLs;                           // R_j [32][LV]
-  float* s_uj = s_rt + kBc * LV;                            // U_j [32][LV]
-  uint64_t* s_anc = reinterpret_cast<uint64_t*>(smem + SM::head + SM::uni);  // [32][kHW]
-  int16_t* s_ord = reinterpret_cast<int16_t*>(s_anc + kBc * kHW);
+  uint16_t* s_xy = reinterpret_cast<uint16_t*>(smem + SM::qk);  // [kCP][-X hi, -X lo, Y hi, Y lo][32][kUL]
+  float* s_d = reinterpret_cast<float*>(smem + SM::qk + SM::xy);  // [2][32][kLs]
+  int16_t* s_ord = reinterpret_cast<int16_t*>(s_d + 2 * kBc * kLs);
   int16_t* s_ppos = s_ord + kHMaxT;
   float* s_lal = reinterpret_cast<float*>(s_ppos + kHMaxT);
   float* s_la = s_lal + kHMaxT;
   float* s_be = s_la + kHMaxT;
+  float* s_a = s_lal;  // a_p, once the partial sums are done
 
-  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  // The G value heads of unit u = (sequence, key head) read the same Gram
+  // blocks: blocks u % 8 + 8 j of their group of 8 G, i.e. one XCD.
   const int T = p.T, Hk = p.Hk, Hv = p.Hv;
-  const int g = h * Hk / Hv;
+  const int G = Hv / Hk;
+  const int grp = blockIdx.x / (8 * G), rem = blockIdx.x % (8 * G);
+  const int unit = 8 * grp + rem % 8;
+  if (unit >= p.B * Hk) return;  // uniform
+  const int b = unit / Hk, g = unit % Hk, h = g * G + rem / 8;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, m = lane >> 4;
   const int nq = Hk * DK;
   const size_t C = size_t(2 * nq + Hv * DV);
-  const MetaPtrs m = meta_ptrs(p.meta, p.B, T);
-  const int W = m.W;
+  const MetaPtrs m_ = meta_ptrs(p.meta, p.B, T);
   const size_t bt = size_t(b) * T;
-  const int nval = m.status[b] == GDN_TREE_OK ? m.nvalid[b] : 0;
+  const int nval = __builtin_amdgcn_readfirstlane(m_.status[b] == GDN_TREE_OK ? m_.nvalid[b] : 0);
+  const int NB = (T + kBc - 1) / kBc, NBv = (nval + kBc - 1) / kBc;
   const TIn* alpha = static_cast<const TIn*>(p.alpha);
   const TIn* beta = static_cast<const TIn*>(p.beta);
-  const float* Fb = p.F + bt * C;
-  float* Ub = p.U + (size_t(b) * Hv + h) * size_t(T) * DV;
+  const float* Fq = p.F + bt * C + g * DK;            // uniform
+  const float* Fv = p.F + bt * C + 2 * nq + h * DV;
+  const uint32_t C4 = uint32_t(C) * 4, H4 = uint32_t(Hv) * DV * 4;  // row bytes
+  const int col = 16 * wave + l16;  // this lane's channel (wave < NTV)
+  const bool chan = wave < NTV;
   float* outb = p.out + bt * size_t(Hv) * DV + size_t(h) * DV;
+  const float* Db = p.D + (size_t(b) * Hv + h) * NB * (2 * kBc * kBc);
+  const float* Gb = p.Gm + (size_t(b) * Hk + g) * (size_t(NB) * (NB - 1) / 2) * (2 * kBc * kBc);
+  // this wave's U; waves without channels load the first wave's (all loads are
+  // unconditional) and store nothing
+  uint16_t* Uw = p.U + (((size_t(b) * Hv + h) * NB) * NTV + (chan ? wave : 0)) * (2 * 64 * 8);
+  constexpr int kUB = NTV * 2 * 64 * 8;  // halves of U per block
 
-  // ---- metadata by position: node, parent position, log alpha, beta
+  // ---- metadata by position: node, parent position, log2 alpha, beta
   for (int j = tid; j < T; j += kHT) {
-    const int nd = m.order[bt + j];
+    const int nd = m_.order[bt + j];
     const bool real = j < nval;
     s_ord[j] = int16_t(nd);
-    s_ppos[j] = int16_t(real ? m.ppos[bt + j] : -1);
-    // log alpha, floored at the smallest normal float so that alpha = 0
+    s_ppos[j] = int16_t(real ? m_.ppos[bt + j] : -1);
+    // log2 alpha, floored at the smallest normal float so that alpha = 0
     // still gives finite ratios a_i / a_j
-    s_lal[j] = real ? fmaxf(logf(ld(alpha, (bt + nd) * Hv + h)), -87.0f) : 0.0f;
+    s_lal[j] = real ? fmaxf(log2f(ld(alpha, (bt + nd) * Hv + h)), kMinLog2) : 0.0f;
     s_be[j] = real ? ld(beta, (bt + nd) * Hv + h) : 0.0f;
   }
+  for (int i = tid; i < (T - nval) * (DV / 4); i += kHT) {  // padding slots
+    const int nd = m_.order[bt + nval + i / (DV / 4)];
+    *reinterpret_cast<float4*>(outb + size_t(nd) * Hv * DV + 4 * (i % (DV / 4))) = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (nval == 0) return;  // uniform
+  // block rows of q~ and k~ -> hi / lo planes, loaded a block ahead
+  float4 qkv[NQK];
+  auto fetch_qk = [&](int jb) {
+    const int tid = opaque(threadIdx.x);
+#pragma unroll
+    for (int j = 0; j < NQK; ++j) {
+      const int i = j * kHT + tid;
+      const int part = i / (kBc * (DK / 4)) & 1, r = i / (DK / 4) % kBc, c4 = i % (DK / 4);
+      const int pos = kBc * jb + r;
+      // clamped rows: every load is unconditional; rows past the tree are
+      // zeroed at the store
+      const size_t off = size_t(uint32_t(pos < nval ? pos : 0)) * C4 + (part ? 4 * nq : 0) + 16 * c4;
+      qkv[j] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Fq) + off);
+    }
+  };
+  auto store_qk = [&](int jb) {
+    const int tid = opaque(threadIdx.x);
+#pragma unroll
+    for (int j = 0; j < NQK; ++j) {
+      const int i = j * kHT + tid;
+      if (i < 2 * kBc * (DK / 4)) {
+        const int part = i / (kBc * (DK / 4)), r = i / (DK / 4) % kBc, c4 = i % (DK / 4);
+        const float4 v = kBc * jb + r < nval ? qkv[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+        st_split4((part ? s_kh : s_qh) + r * LKH + 4 * c4, (part ? s_kl : s_ql) + r * LKH + 4 * c4, v);
+      }
+    }
+    if constexpr (DK < KP) {  // zero padding of the contraction
+      for (int i = tid; i < 4 * kBc * (KP - DK); i += kHT)
+        s_qh[i / (KP - DK) * LKH + DK + i % (KP - DK)] = 0;
+    }
+  };
+  // top of a block, loaded a block ahead: the earlier blocks that hold an
+  // ancestor of one of its nodes, its values, its diagonal matrices
+  int flag;
+  f32x4 vop[2];
+  float4 dg;
+  auto fetch_top = [&](int jb) {
+    const int tid = opaque(threadIdx.x), lane = tid & 63, l16 = lane & 15, m = lane >> 4;
+    flag = p.need[(size_t(b) * NB + jb) * kMaxNB + (lane < jb ? lane : 0)];
+    dg = *reinterpret_cast<const float4*>(Db + size_t(jb) * (2 * kBc * kBc) + 4 * tid);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int pos = kBc * jb + 16 * t + 4 * m + e;
+        const size_t off = size_t(uint32_t(pos < nval ? pos : 0)) * C4 + 4 * (chan ? 16 * wave + l16 : l16);
+        vop[t][e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Fv) + off);
+      }
+  };
+  static_assert(kHT * 4 == 2 * kBc * kBc, "a float4 of the diagonal matrices per thread");
+  fetch_qk(0);
+  fetch_top(0);
+  // ---- this wave's rows of S0 as operands: channel 16 wave + l16, columns
+  //      32 ks + 8 m .. + 7
+  bf16x8 sh[NKS], sl_[NKS];
+  {
+    const float* S0 = p.S0 + (size_t(b) * Hv + h) * size_t(DV) * DK + size_t(chan ? col : 0) * DK;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      float x[8];
+      const int k0 = DK < 32 ? 8 * (m & 1) : 32 * ks + 8 * m;
+      const float4 u = *reinterpret_cast<const float4*>(S0 + k0), v = *reinterpret_cast<const float4*>(S0 + k0 + 4);
+      const bool in = DK >= 32 || m < 2;
+      x[0] = in ? u.x : 0.f; x[1] = in ? u.y : 0.f; x[2] = in ? u.z : 0.f; x[3] = in ? u.w : 0.f;
+      x[4] = in ? v.x : 0.f; x[5] = in ? v.y : 0.f; x[6] = in ? v.z : 0.f; x[7] = in ? v.w : 0.f;
+      split8(x, sh[ks], sl_[ks]);
+    }
+  }
   __syncthreads();
-  // log a_p: sum of log alpha over the path root..p, by pointer jumping
+  // log2 a_p: sum of log2 alpha over the path root..p, by pointer jumping
   // (ceil(log2 T) rounds instead of a walk of depth(p) steps per position;
   // s_lal and s_ppos are rewritten to partial sums and 2^r-th ancestors)
   static_assert(kHT >= kHMaxT, "one position per thread");
@@ -227,381 +568,175 @@ __global__ __launch_bounds__(kHT) void chunk_kernel(ChunkParams p) {
       }
       __syncthreads();
     }
-    if (tid < T) s_la[tid] = sl;
+    s_la[tid] = sl;  // 0 past the tree
+    s_a[tid] = tid < nval ? __builtin_amdgcn_exp2f(sl) : 0.0f;
+    if (tid >= nval) s_be[tid] = 0.0f;
   }
-  if (nval > 0) {
-    const float* S0 = p.S0 + (size_t(b) * Hv + h) * size_t(DV) * DK;
-    constexpr int NS4 = (DV * DK / 4 + kHT - 1) / kHT;  // float4 per thread, all in flight
-    float4 sv[NS4];
-#pragma unroll
-    for (int j = 0; j < NS4; ++j) {
-      const int i = j * kHT + tid < DV * DK / 4 ? j * kHT + tid : 0;
-      sv[j] = *reinterpret_cast<const float4*>(S0 + size_t(i / (DK / 4)) * DK + 4 * (i % (DK / 4)));
-    }
-#pragma unroll
-    for (int j = 0; j < NS4; ++j) {
-      const int i = j * kHT + tid;
-      if (i < DV * DK / 4) {
-        const int r = i / (DK / 4), c4 = i % (DK / 4);
-        st_split4(s_s0h + r * LKH + 4 * c4, s_s0l + r * LKH + 4 * c4, sv[j]);
-      }
-    }
-    if constexpr (DK < KP) {  // zero padding of the contraction
-      for (int i = tid; i < DV * (KP - DK); i += kHT) {
-        const int r = i / (KP - DK), c = DK + i % (KP - DK);
-        s_s0h[r * LKH + c] = 0;
-        s_s0l[r * LKH + c] = 0;
-      }
-      for (int i = tid; i < 4 * kBc * (KP - DK); i += kHT) {
-        const int r = i / (KP - DK), c = DK + i % (KP - DK);
-        s_qh[r * LKH + c] = 0;  // q and k planes are contiguous: rows 0 .. 4 kBc - 1
-      }
-    }
-  }
-  __syncthreads();
 
-  const int NB = (T + kBc - 1) / kBc, NBv = (nval + kBc - 1) / kBc;
-  // block rows of q~ and k~ (zero past the tree) -> hi / lo planes: the
-  // loads of a block go to registers first (all in flight together, issued
-  // a block ahead where the planes are still in use), then to the planes
-  constexpr int NQK = (2 * kBc * (DK / 4) + kHT - 1) / kHT;
-  float4 qkv[NQK];
-  auto fetch_qk = [&](int jb) {
+  // ---- cascade over the blocks
+  static_assert(kHT == kBc * kBc / 2, "two elements of a block per thread");
+  const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+  for (int jb = 0; jb < NBv; ++jb) {
+    // lane roles that the compiler cannot see through: addresses are formed
+    // where they are used, not kept over the loop and spilled
+    const int tid = opaque(threadIdx.x), lane = tid & 63, l16 = lane & 15, m = lane >> 4;
+    const int col = 16 * wave + l16;
+    const int xi = tid / (kBc / 2), xc = 2 * (tid % (kBc / 2));  // this thread's X, Y elements: row, columns xc, xc + 1
+    uint32_t need = uint32_t(__ballot(lane < jb && flag != 0));
+    // Gram blocks of a group, two elements of each per thread
+    float2 gx[kCP], gy[kCP];
+    uint32_t gm[kCP];
+    int cs[kCP];
+    auto fetch_group = [&] {
 #pragma unroll
-    for (int j = 0; j < NQK; ++j) {
-      const int i = j * kHT + tid;
-      const int part = i / (kBc * (DK / 4)), rem = i % (kBc * (DK / 4));
-      const int r = rem / (DK / 4), c4 = rem % (DK / 4);
-      const int pos = kBc * jb + r;
-      // clamped rows: every load is unconditional; rows past the tree are
-      // zeroed at the store
-      const int pc = pos < nval ? pos : 0;
-      qkv[j] = *reinterpret_cast<const float4*>(Fb + pc * C + (part ? nq : 0) + g * DK + 4 * c4);
-    }
-  };
-  auto store_qk = [&](int jb) {
-#pragma unroll
-    for (int j = 0; j < NQK; ++j) {
-      const int i = j * kHT + tid;
-      if (i < 2 * kBc * (DK / 4)) {
-        const int part = i / (kBc * (DK / 4)), rem = i % (kBc * (DK / 4));
-        const int r = rem / (DK / 4), c4 = rem % (DK / 4);
-        const float4 v = kBc * jb + r < nval ? qkv[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-        st_split4((part ? s_kh : s_qh) + r * LKH + 4 * c4, (part ? s_kl : s_ql) + r * LKH + 4 * c4, v);
+      for (int q = 0; q < kCP; ++q) {
+        cs[q] = need ? __ffs(int(need)) - 1 : -1;
+        need &= need - 1u;
+        const int c = cs[q] >= 0 ? cs[q] : 0;  // loads without a branch, unused where there is no block
+        const float* gp = Gb + (size_t(jb) * (jb - 1) / 2 + c) * (2 * kBc * kBc) + xi * kBc + xc;
+        gx[q] = *reinterpret_cast<const float2*>(gp);
+        gy[q] = *reinterpret_cast<const float2*>(gp + kBc * kBc);
+        gm[q] = p.mask[((size_t(b) * NB + jb) * kMaxNB + c) * kBc + xi];
       }
-    }
-  };
-
-  // ---- phase A: a Q S0^T -> out, beta (V - a K S0^T) -> U
-  constexpr int NTA = (2 * NTILE + kHT / 64 - 1) / (kHT / 64);  // tasks per wave
-  if (NBv > 0) fetch_qk(0);
-  for (int jb = 0; jb < NB; ++jb) {
-    if (jb < NBv) {
-      store_qk(jb);
-      if (jb + 1 < NBv) fetch_qk(jb + 1);  // in flight during this block's products
-      // the value operands of this wave's K S0^T tasks, loaded ahead
-      float vop[NTA][4];
+    };
+    fetch_group();
+    __syncthreads();  // LDS of the block before is read (first block: s_la is written)
+    store_qk(jb);
+    *reinterpret_cast<float4*>(s_d + tid / 8 * kLs + 4 * (tid % 8)) = dg;  // tile (0, 1) of neither is read
+    __syncthreads();
+    // ---- O_j = a Q S0^T, R_j = beta (V - a K S0^T)
+    f32x4 rr[2] = {z4, z4}, oo[2] = {z4, z4};
+    if (chan) {
 #pragma unroll
-      for (int ta = 0; ta < NTA; ++ta) {
-        const int task = wave + ta * (kHT / 64);
-        const int t = task % NTILE, ti = t / NTV, tj = t % NTV, col = 16 * tj + (lane & 15);
+      for (int t = 0; t < 2; ++t) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int pos = kBc * jb + 16 * ti + 4 * (lane >> 4) + r;
-          vop[ta][r] = Fb[(pos < nval ? pos : 0) * C + 2 * nq + h * DV + col];
+        for (int ks = 0; ks < NKS; ++ks) {
+          const int o = (16 * t + l16) * LKH + 32 * ks + 8 * m;
+          oo[t] = mfma3(*reinterpret_cast<const bf16x8*>(s_qh + o), *reinterpret_cast<const bf16x8*>(s_ql + o), sh[ks],
+                        sl_[ks], oo[t]);
+          rr[t] = mfma3(*reinterpret_cast<const bf16x8*>(s_kh + o), *reinterpret_cast<const bf16x8*>(s_kl + o), sh[ks],
+                        sl_[ks], rr[t]);
+        }
+        const int p0 = kBc * jb + 16 * t + 4 * m;
+        const f32x4 a = as_x4(*reinterpret_cast<const float4*>(s_a + p0));
+        const f32x4 be = as_x4(*reinterpret_cast<const float4*>(s_be + p0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          oo[t][e] = a[e] * oo[t][e];
+          rr[t][e] = be[e] * (vop[t][e] - a[e] * rr[t][e]);
+        }
+        if (kBc * jb + kBc > nval) {  // uniform: rows past the tree
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (p0 + e >= nval) oo[t][e] = rr[t][e] = 0.0f;
         }
       }
+    }
+    // ---- R_j -= X_jc U_c, O_j += Y_jc U_c, kCP blocks c at a time
+    while (cs[0] >= 0) {
+      bf16x8 uh[kCP], ul[kCP];
+#pragma unroll
+      for (int q = 0; q < kCP; ++q) {
+        const uint16_t* up = Uw + size_t(cs[q] >= 0 ? cs[q] : 0) * kUB + 8 * lane;
+        uh[q] = *reinterpret_cast<const bf16x8*>(up);
+        ul[q] = *reinterpret_cast<const bf16x8*>(up + 64 * 8);
+      }
+      const int pi = kBc * jb + xi;
+      const float la = s_la[pi], be = s_be[pi];  // rows past the tree: no ancestors
+#pragma unroll
+      for (int q = 0; q < kCP; ++q) {
+        if (cs[q] < 0) break;  // uniform
+        const float2 lc = *reinterpret_cast<const float2*>(s_la + kBc * cs[q] + xc);
+        float x[2] = {gx[q].x, gx[q].y}, y[2] = {gy[q].x, gy[q].y};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const bool anc = (gm[q] >> (xc + e)) & 1u;
+          const float r = __builtin_amdgcn_exp2f(la - (e ? lc.y : lc.x));
+          x[e] = anc ? -be * (r * x[e]) : 0.0f;
+          y[e] = anc ? r * y[e] : 0.0f;
+        }
+        uint16_t* pl = s_xy + q * 4 * kPl + xi * kUL + slot_col(xc);
+        st_split2(pl, pl + kPl, x[0], x[1]);
+        st_split2(pl + 2 * kPl, pl + 3 * kPl, y[0], y[1]);
+      }
+      const bool second = cs[kCP - 1] >= 0;  // uniform
+      fetch_group();  // the next group's loads fly during this one
       __syncthreads();
+      if (chan) {
 #pragma unroll
-      for (int ta = 0; ta < NTA; ++ta) {
-        const int task = wave + ta * (kHT / 64);
-        if (task >= 2 * NTILE) continue;  // uniform per wave
-        const int kind = task / NTILE, t = task % NTILE;
-        const int ti = t / NTV, tj = t % NTV;
-        const f32x4 acc = mm16x3<KP>((kind ? s_kh : s_qh) + 16 * ti * LKH, (kind ? s_kl : s_ql) + 16 * ti * LKH,
-                                     LKH, s_s0h + 16 * tj * LKH, s_s0l + 16 * tj * LKH, LKH, zero4(), lane);
-        const int col = 16 * tj + (lane & 15);
+        for (int q = 0; q < kCP; ++q) {
+          if (q > 0 && !second) break;  // uniform
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int pos = kBc * jb + 16 * ti + 4 * (lane >> 4) + r;
-          if (pos >= T) continue;
-          const bool real = pos < nval;
-          const float a = real ? expf(s_la[pos]) : 0.0f;
-          if (kind == 0) {
-            outb[size_t(s_ord[pos]) * Hv * DV + col] = real ? a * acc[r] : 0.0f;
-          } else {
-            Ub[size_t(pos) * DV + col] = real ? s_be[pos] * (vop[ta][r] - a * acc[r]) : 0.0f;
+          for (int t = 0; t < 2; ++t) {
+            const uint16_t* pl = s_xy + q * 4 * kPl + (16 * t + l16) * kUL + 8 * m;
+            rr[t] = mfma3(*reinterpret_cast<const bf16x8*>(pl), *reinterpret_cast<const bf16x8*>(pl + kPl), uh[q],
+                          ul[q], rr[t]);
+            oo[t] = mfma3(*reinterpret_cast<const bf16x8*>(pl + 2 * kPl),
+                          *reinterpret_cast<const bf16x8*>(pl + 3 * kPl), uh[q], ul[q], oo[t]);
           }
         }
       }
-      __syncthreads();
-    } else {  // all padding
-      for (int i = tid; i < kBc * DV; i += kHT) {
-        const int pos = kBc * jb + i / DV;
-        if (pos < T) outb[size_t(s_ord[pos]) * Hv * DV + i % DV] = 0.0f;
-      }
+      if (cs[0] >= 0) __syncthreads();  // uniform: the planes are read
     }
-  }
-  __syncthreads();  // S0 region reused below
-  if constexpr (DK < KP) {
-    for (int i = tid; i < 2 * kBc * (KP - DK); i += kHT) {
-      const int r = i / (KP - DK), c = DK + i % (KP - DK);
-      s_kch[r * LKH + c] = 0;  // hi and lo planes are contiguous
-    }
-  }
-
-  // ---- phase B: forward substitution over the blocks
-  // block-top inputs of block jb (the ancestor words of its rows, R_j and
-  // the a Q S0^T part of O_j from phase A), loaded a block ahead: every load
-  // is unconditional (clamped rows), padding is zeroed when they are used
-  constexpr int NAW = (kBc * kHW + kHT - 1) / kHT;
-  uint64_t awpf[NAW];
-  f32x4 rrpf[2], oopf[2];
-  auto fetch_top = [&](int jb) {
-#pragma unroll
-    for (int j = 0; j < NAW; ++j) {
-      const int i = j * kHT + tid;
-      const int r = (i / kHW) % kBc, w = i % kHW;
-      const int pos = kBc * jb + r;
-      awpf[j] = m.anc[(bt + s_ord[pos < nval ? pos : 0]) * W + (w < W ? w : 0)];
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = (wave + 8 * u) % NTILE;
-      const int ti = t / NTV, tj = t % NTV, col = 16 * tj + (lane & 15);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int pos = kBc * jb + 16 * ti + 4 * (lane >> 4) + r;
-        const int pc = pos < nval ? pos : 0;
-        rrpf[u][r] = Ub[size_t(pc) * DV + col];
-        oopf[u][r] = outb[size_t(s_ord[pc]) * Hv * DV + col];
-      }
-    }
-  };
-  if (NBv > 0) {
-    fetch_qk(0);
-    fetch_top(0);
-  }
-  for (int jb = 0; jb < NBv; ++jb) {
-    store_qk(jb);
-#pragma unroll
-    for (int j = 0; j < NAW; ++j) {
-      const int i = j * kHT + tid;
-      if (i < kBc * kHW) {
-        const int r = i / kHW, w = i % kHW;
-        s_anc[i] = (kBc * jb + r < nval && w < W) ? awpf[j] : 0ull;
-      }
-    }
-    f32x4 rr[2], oo[2];  // R_j and O_j tiles of this wave: t = wave, wave + 8
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = wave + 8 * u;
-      const int ti = (t % NTILE) / NTV;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool live = t < NTILE && kBc * jb + 16 * ti + 4 * (lane >> 4) + r < nval;
-        rr[u][r] = live ? rrpf[u][r] : 0.0f;
-        oo[u][r] = live ? oopf[u][r] : 0.0f;
-      }
-    }
-    __syncthreads();
-    // the earlier blocks that hold an ancestor of a node of this block (one
-    // bit per block); their keys and U rows are loaded one block ahead
-    if (tid == 0) s_need = 0u;
-    __syncthreads();
-    {
-      uint32_t mask = 0u;
-      for (int pr = tid; pr < kBc * kBc * jb; pr += kHT) {
-        const int i = pr % kBc, pc = pr / kBc;
-        if (kBc * jb + i < nval && pc < nval) {
-          const int nd = s_ord[pc];
-          if ((s_anc[i * kHW + (nd >> 6)] >> (nd & 63)) & 1ull) mask |= 1u << (pc / kBc);
-        }
-      }
-      if (mask) atomicOr(&s_need, mask);
-    }
-    __syncthreads();
-    uint32_t need = s_need;
-    float4 kpf[NKP], upf[NUP];
-    auto fetch = [&](int cb) {
-#pragma unroll
-      for (int j = 0; j < NKP; ++j) {
-        const int i = j * kHT + tid;
-        const int r = i < kBc * (DK / 4) ? i / (DK / 4) : 0, c4 = i < kBc * (DK / 4) ? i % (DK / 4) : 0;
-        kpf[j] = *reinterpret_cast<const float4*>(Fb + (kBc * cb + r) * C + nq + g * DK + 4 * c4);
-      }
-#pragma unroll
-      for (int j = 0; j < NUP; ++j) {
-        const int i = j * kHT + tid;
-        const int r = i < kBc * (DV / 4) ? i % kBc : 0, c4 = i < kBc * (DV / 4) ? i / kBc : 0;
-        upf[j] = *reinterpret_cast<const float4*>(Ub + size_t(kBc * cb + r) * DV + 4 * c4);
-      }
-    };
-    int cb = need ? __ffs(int(need)) - 1 : -1;
-    if (cb >= 0) fetch(cb);
-    while (cb >= 0) {
-#pragma unroll
-      for (int j = 0; j < NKP; ++j) {
-        const int i = j * kHT + tid;
-        if (i < kBc * (DK / 4)) {
-          const int r = i / (DK / 4), c4 = i % (DK / 4);
-          st_split4(s_kch + r * LKH + 4 * c4, s_kcl + r * LKH + 4 * c4, kpf[j]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NUP; ++j) {  // U_c transposed: [dv][node]
-        const int i = j * kHT + tid;
-        if (i < kBc * (DV / 4)) {
-          const int r = i % kBc, c4 = i / kBc;
-          const float4 u = upf[j];
-          st_split1(s_uth + (4 * c4) * UL + r, s_utl + (4 * c4) * UL + r, u.x);
-          st_split1(s_uth + (4 * c4 + 1) * UL + r, s_utl + (4 * c4 + 1) * UL + r, u.y);
-          st_split1(s_uth + (4 * c4 + 2) * UL + r, s_utl + (4 * c4 + 2) * UL + r, u.z);
-          st_split1(s_uth + (4 * c4 + 3) * UL + r, s_utl + (4 * c4 + 3) * UL + r, u.w);
-        }
-      }
-      need &= need - 1u;
-      const int nb = need ? __ffs(int(need)) - 1 : -1;
-      if (nb >= 0) fetch(nb);  // the next block's loads fly during this one
-      __syncthreads();
-      {  // -X_jc (waves 0-3) and Y_jc (waves 4-7), one 16 x 16 tile each
-        const int kind = wave >> 2, ti = (wave >> 1) & 1, tc = wave & 1;
-        const f32x4 acc = mm16x3<KP>((kind ? s_qh : s_kh) + 16 * ti * LKH, (kind ? s_ql : s_kl) + 16 * ti * LKH,
-                                     LKH, s_kch + 16 * tc * LKH, s_kcl + 16 * tc * LKH, LKH, zero4(), lane);
-        const int c = 16 * tc + (lane & 15), pc = kBc * cb + c;
-        const int nd = s_ord[pc];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * ti + 4 * (lane >> 4) + r, pi = kBc * jb + i;
-          float val = 0.0f;
-          if (pi < nval && pc < nval && ((s_anc[i * kHW + (nd >> 6)] >> (nd & 63)) & 1ull))
-            val = expf(s_la[pi] - s_la[pc]) * acc[r];
-          if (kind == 0)
-            st_split1(s_xh + i * UL + c, s_xl + i * UL + c, -(pi < nval ? s_be[pi] : 0.0f) * val);
-          else
-            st_split1(s_yh + i * UL + c, s_yl + i * UL + c, val);
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int t = wave + 8 * u;
-        if (t < NTILE) {
-          const int ti = t / NTV, tj = t % NTV;
-          rr[u] = mm16x3<kBc>(s_xh + 16 * ti * UL, s_xl + 16 * ti * UL, UL, s_uth + 16 * tj * UL,
-                              s_utl + 16 * tj * UL, UL, rr[u], lane);
-          oo[u] = mm16x3<kBc>(s_yh + 16 * ti * UL, s_yl + 16 * ti * UL, UL, s_uth + 16 * tj * UL,
-                              s_utl + 16 * tj * UL, UL, oo[u], lane);
-        }
-      }
-      __syncthreads();
-      cb = nb;
-    }
-    // ---- diagonal block: A = -X_jj, M0 = I + A, Y_jj; R_j -> LDS
-    {
-      const int kind = wave >> 2, ti = (wave >> 1) & 1, tc = wave & 1;
-      const f32x4 acc = mm16x3<KP>((kind ? s_qh : s_kh) + 16 * ti * LKH, (kind ? s_ql : s_kl) + 16 * ti * LKH,
-                                   LKH, s_kh + 16 * tc * LKH, s_kl + 16 * tc * LKH, LKH, zero4(), lane);
-      const int c = 16 * tc + (lane & 15), pc = kBc * jb + c;
-      const int nd = s_ord[pc];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * ti + 4 * (lane >> 4) + r, pi = kBc * jb + i;
-        const bool anc = pi < nval && pc < nval && ((s_anc[i * kHW + (nd >> 6)] >> (nd & 63)) & 1ull);
-        if (kind == 0) {
-          const float av = anc ? -s_be[pi] * expf(s_la[pi] - s_la[pc]) * acc[r] : 0.0f;
-          s_pa[i * kLs + c] = av;
-          s_ma[i * kLs + c] = av + (i == c ? 1.0f : 0.0f);
-        } else {
-          s_y[i * kLs + c] = (anc || (i == c && pi < nval)) ? expf(s_la[pi] - s_la[pc]) * acc[r] : 0.0f;
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = wave + 8 * u;
-      if (t < NTILE) {
-        const int ti = t / NTV, tj = t % NTV, col = 16 * tj + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s_rt[(16 * ti + 4 * (lane >> 4) + r) * LV + col] = rr[u][r];
-      }
-    }
-    __syncthreads();
-    // this block's q / k planes are read for the last time above: the next
-    // block's rows and block-top inputs load during the inverse
     if (jb + 1 < NBv) {
       fetch_qk(jb + 1);
       fetch_top(jb + 1);
     }
-    // ---- (I + X_jj)^-1 = (I + A)(I + A^2)(I + A^4)(I + A^8)(I + A^16):
-    //      round s: waves 0-3 square the power of A, waves 4-7 multiply the
-    //      partial product by (I + the power formed in round s - 1)
-    {
-      const int ti = (wave >> 1) & 1, tj = wave & 1;
-      float* pw[2] = {s_pa, s_pb};
-      float* mp[2] = {s_ma, s_mb};
-#pragma unroll
-      for (int s = 1; s <= 5; ++s) {
-        if (wave < 4) {
-          if (s <= 4) {
-            const float* src = pw[(s - 1) & 1];
-            const f32x4 d = mm16<kBc, false>(src + 16 * ti * kLs, kLs, src + 16 * tj, kLs, zero4(), lane);
-            st_tile(pw[s & 1], ti, tj, lane, d);
-          }
-        } else if (s >= 2) {
-          const float* msrc = mp[s & 1];          // M_{s-2}
-          const float* psrc = pw[(s - 1) & 1];    // A^(2^(s-1))
-          f32x4 d = ld_tile(msrc, ti, tj, lane);
-          d = mm16<kBc, false>(msrc + 16 * ti * kLs, kLs, psrc + 16 * tj, kLs, d, lane);
-          st_tile(mp[(s + 1) & 1], ti, tj, lane, d);
-        }
-        __syncthreads();
+    // ---- U_j = (I + X_jj)^-1 R_j, kept as operands of the later blocks
+    if (chan) {
+      const float* vp = s_d + l16 * kLs + 4 * m;
+      const float* yp = vp + kBc * kLs;
+      auto tile = [](const float* q) { return as_x4(*reinterpret_cast<const float4*>(q)); };
+      const f32x4 v00 = tile(vp), v10 = tile(vp + 16 * kLs), v11 = tile(vp + 16 * kLs + 16);
+      const f32x4 y00 = tile(yp), y10 = tile(yp + 16 * kLs), y11 = tile(yp + 16 * kLs + 16);
+      const f32x4 u0 = mm_f(v00, rr[0], z4), u1 = mm_f(v11, rr[1], mm_f(v10, rr[0], z4));
+      {
+        const float x[8] = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
+        bf16x8 hi, lo;
+        split8(x, hi, lo);
+        *reinterpret_cast<bf16x8*>(Uw + size_t(jb) * kUB + 8 * lane) = hi;
+        *reinterpret_cast<bf16x8*>(Uw + size_t(jb) * kUB + 64 * 8 + 8 * lane) = lo;
       }
-    }
-    // the inverse is in s_ma (M_4); U_j = M_4 R_j -> LDS and the workspace
+      // ---- O_j += Y_jj U_j, scaled and stored
+      oo[0] = mm_f(y00, u0, oo[0]);
+      oo[1] = mm_f(y11, u1, mm_f(y10, u0, oo[1]));
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = wave + 8 * u;
-      if (t < NTILE) {
-        const int ti = t / NTV, tj = t % NTV, col = 16 * tj + (lane & 15);
-        const f32x4 d = mm16<kBc, false>(s_ma + 16 * ti * kLs, kLs, s_rt + 16 * tj, LV, zero4(), lane);
+      for (int t = 0; t < 2; ++t) {
+        const int p0 = kBc * jb + 16 * t + 4 * m;
+        const short4 nd = *reinterpret_cast<const short4*>(s_ord + p0);
+        const int nn[4] = {nd.x, nd.y, nd.z, nd.w};
+        // stores without a branch (a branch would make the next block wait for
+        // all of them): rows past the tree are zero, those past T, in the last
+        // block, go to this lane's U, which nothing reads any more
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = 16 * ti + 4 * (lane >> 4) + r, pos = kBc * jb + row;
-          s_uj[row * LV + col] = d[r];
-          if (pos < T) Ub[size_t(pos) * DV + col] = d[r];
+        for (int e = 0; e < 4; ++e) {
+          float* o = reinterpret_cast<float*>(reinterpret_cast<char*>(outb) + size_t(uint32_t(nn[e])) * H4) + col;
+          float* spare = reinterpret_cast<float*>(Uw + size_t(jb) * kUB + 8 * lane);
+          *(p0 + e < T ? o : spare) = p0 + e < nval ? p.scale * oo[t][e] : 0.0f;
         }
       }
     }
-    __syncthreads();
-    // ---- O_j += Y_jj U_j, scaled and stored
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int t = wave + 8 * u;
-      if (t < NTILE) {
-        const int ti = t / NTV, tj = t % NTV, col = 16 * tj + (lane & 15);
-        const f32x4 d = mm16<kBc, false>(s_y + 16 * ti * kLs, kLs, s_uj + 16 * tj, LV, oo[u], lane);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int pos = kBc * jb + 16 * ti + 4 * (lane >> 4) + r;
-          if (pos < nval) outb[size_t(s_ord[pos]) * Hv * DV + col] = p.scale * d[r];
-        }
-      }
-    }
-    __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------------------
-// Launch: features, then the chunked kernel
+// Launch: features, Gram blocks, cascade
 // ---------------------------------------------------------------------------
 template <int DK, int DV, typename TIn>
 static int launch_chunk_t(const ChunkParams& p, hipStream_t stream) {
   using SM = ChunkSmem<DK, DV>;
-  const int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_kernel<DK, DV, TIn>), int(SM::total),
-                                    "verify_chunked");
+  using SG = GramSmem<DK>;
+  int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_kernel<DK, DV, TIn>), int(SM::total),
+                              "verify_chunked");
   if (rc != GDN_OK) return rc;
-  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), dim3(p.Hv, p.B), dim3(kHT), SM::total, stream, p);
+  rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_gram_kernel<DK, TIn>), int(SG::total),
+                          "verify_chunked");
+  if (rc != GDN_OK) return rc;
+  const int NB = (p.T + kBc - 1) / kBc, G = p.Hv / p.Hk, units = p.B * p.Hk;
+  int groups = 0;
+  for (int j = 0; j < NB; ++j) groups += j / kCG + 1;
+  hipLaunchKernelGGL((chunk_gram_kernel<DK, TIn>), dim3(groups, p.Hk, p.B), dim3(kHT), SG::total, stream, p);
+  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), dim3((units + 7) / 8 * 8 * G), dim3(kHT), SM::total, stream, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(GDN_EHIP, "verify_chunked launch: %s", hipGetErrorString(e));
   return GDN_OK;
@@ -641,6 +776,7 @@ int launch_verify_chunked(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStr
   p.T = a.T;
   p.Hk = a.Hk;
   p.Hv = a.Hv;
+  p.dv = a.dv;
   p.scale = a.scale;
   p.meta = a.meta;
   p.alpha = a.alpha;
@@ -648,7 +784,13 @@ int launch_verify_chunked(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStr
   p.S0 = a.S0;
   p.out = a.out;
   p.F = F;
-  p.U = F + features_f32_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv) / sizeof(float);
+  const ChunkSizes z(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv);
+  unsigned char* w = static_cast<unsigned char*>(ws) + z.f;
+  p.D = reinterpret_cast<float*>(w);
+  p.Gm = reinterpret_cast<float*>(w += z.d);
+  p.mask = reinterpret_cast<uint32_t*>(w += z.g);
+  p.need = w += z.k;
+  p.U = reinterpret_cast<uint16_t*>(w += z.n);
   if (a.in_dtype == GDN_BF16) return chunk_dk<BF16>(a.dk, a.dv, p, stream);
   return chunk_dk<float>(a.dk, a.dv, p, stream);
 }

@@ -92,8 +92,8 @@ def _instrument_chunked(src: str) -> str:
             raise RuntimeError(f"phase_clocks: anchor not found once: {old[:70]!r}")
         src = src.replace(old, new)
 
-    rep("  float* U;        // [B][Hv][T][DV]: right-hand sides, then the solved rows\n};",
-        "  float* U;        // [B][Hv][T][DV]: right-hand sides, then the solved rows\n"
+    rep("  uint16_t* U;     // [B][Hv][NB][DV / 16][2][64][8]: solved rows, bf16 hi and lo, per lane\n};",
+        "  uint16_t* U;     // [B][Hv][NB][DV / 16][2][64][8]: solved rows, bf16 hi and lo, per lane\n"
         "  unsigned long long* stamps;\n  long long stamp_cap;\n};")
     rep("namespace gdn {\n",
         "namespace gdn {\n"
@@ -101,25 +101,25 @@ def _instrument_chunked(src: str) -> str:
         "if (p.stamps && lin_ < p.stamp_cap && threadIdx.x == 0 && (k) < 128) "
         "p.stamps[lin_ * 128 + (k)] = __builtin_amdgcn_s_memtime(); } while (0)\n"
         "static unsigned long long* g_stamps = nullptr;\nstatic long long g_stamp_cap = 0;\n")
-    rep("  // ---- metadata by position: node, parent position, log alpha, beta\n",
-        "  TS(0);\n  // ---- metadata by position: node, parent position, log alpha, beta\n")
-    rep("  // ---- phase A: a Q S0^T -> out, beta (V - a K S0^T) -> U\n",
-        "  TS(1);\n  // ---- phase A: a Q S0^T -> out, beta (V - a K S0^T) -> U\n")
-    rep("  // ---- phase B: forward substitution over the blocks\n",
-        "  TS(2);\n  // ---- phase B: forward substitution over the blocks\n")
-    rep("  for (int jb = 0; jb < NBv; ++jb) {\n    store_qk(jb);\n",
-        "  for (int jb = 0; jb < NBv; ++jb) {\n    TS(4 + 4 * jb);\n    store_qk(jb);\n")
-    rep("    // ---- diagonal block: A = -X_jj, M0 = I + A, Y_jj; R_j -> LDS\n",
-        "    TS(5 + 4 * jb);\n    // ---- diagonal block: A = -X_jj, M0 = I + A, Y_jj; R_j -> LDS\n")
-    rep("    // the inverse is in s_ma (M_4); U_j = M_4 R_j -> LDS and the workspace\n",
-        "    TS(6 + 4 * jb);\n    // the inverse is in s_ma (M_4); U_j = M_4 R_j -> LDS and the workspace\n")
-    rep("    // ---- O_j += Y_jj U_j, scaled and stored\n",
-        "    TS(7 + 4 * jb);\n    // ---- O_j += Y_jj U_j, scaled and stored\n")
-    rep("    __syncthreads();\n  }\n}\n\n// ---------------------------------------------------------------------------\n// Launch: features",
-        "    __syncthreads();\n  }\n  TS(127);\n}\n\n// ---------------------------------------------------------------------------\n// Launch: features")
-    rep("  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), dim3(p.Hv, p.B), dim3(kHT), SM::total, stream, p);",
-        "  const_cast<ChunkParams&>(p).stamps = g_stamps;\n  const_cast<ChunkParams&>(p).stamp_cap = g_stamp_cap;\n"
-        "  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), dim3(p.Hv, p.B), dim3(kHT), SM::total, stream, p);")
+    rep("  // ---- metadata by position: node, parent position, log2 alpha, beta\n",
+        "  TS(0);\n  // ---- metadata by position: node, parent position, log2 alpha, beta\n")
+    rep("  // log2 a_p: sum of log2 alpha over the path root..p, by pointer jumping\n",
+        "  TS(1);\n  // log2 a_p: sum of log2 alpha over the path root..p, by pointer jumping\n")
+    rep("  // ---- cascade over the blocks\n",
+        "  TS(2);\n  // ---- cascade over the blocks\n")
+    rep("    __syncthreads();  // LDS of the block before is read (first block: s_la is written)\n",
+        "    TS(4 + 4 * jb);\n    __syncthreads();  // LDS of the block before is read (first block: s_la is written)\n")
+    rep("    // ---- R_j -= X_jc U_c, O_j += Y_jc U_c, kCP blocks c at a time\n",
+        "    TS(5 + 4 * jb);\n    // ---- R_j -= X_jc U_c, O_j += Y_jc U_c, kCP blocks c at a time\n")
+    rep("    // ---- U_j = (I + X_jj)^-1 R_j, kept as operands of the later blocks\n",
+        "    TS(6 + 4 * jb);\n    // ---- U_j = (I + X_jj)^-1 R_j, kept as operands of the later blocks\n")
+    rep("      // ---- O_j += Y_jj U_j, scaled and stored\n",
+        "      TS(7 + 4 * jb);\n      // ---- O_j += Y_jj U_j, scaled and stored\n")
+    rep("      }\n    }\n  }\n}\n\n// ---------------------------------------------------------------------------\n// Launch: features",
+        "      }\n    }\n  }\n  TS(127);\n}\n\n// ---------------------------------------------------------------------------\n// Launch: features")
+    launch = "  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), dim3((units + 7) / 8 * 8 * G), dim3(kHT), SM::total, stream, p);"
+    rep(launch,
+        "  const_cast<ChunkParams&>(p).stamps = g_stamps;\n  const_cast<ChunkParams&>(p).stamp_cap = g_stamp_cap;\n" + launch)
     src += ('\nextern "C" void gdn_chunk_stamps(void* buf, long long cap_blocks) {\n'
             '  gdn::g_stamps = static_cast<unsigned long long*>(buf);\n'
             '  gdn::g_stamp_cap = buf ? cap_blocks : 0;\n}\n')
@@ -173,17 +173,17 @@ def _run_chunked(args, G, W, np, torch, ctypes) -> int:
     st = stamps.view(blocks, CSLOT).cpu().numpy().astype(np.float64)
     st = st[st[:, 0] > 0]
     nb = (w.T + 31) // 32
-    rows = {"metadata": st[:, 1] - st[:, 0], "phase A (a Q S0^T, beta (V - a K S0^T))": st[:, 2] - st[:, 1]}
-    acc = {"block tops and pairs with earlier blocks": 0.0, "diagonal block and its inverse": 0.0,
-           "U_j": 0.0, "O_j stores (to the next block)": 0.0}
+    rows = {"metadata, S0 operands": st[:, 1] - st[:, 0], "path decays": st[:, 2] - st[:, 1]}
+    acc = {"block tops, S0 products": 0.0, "pairs with earlier blocks": 0.0,
+           "U_j": 0.0, "Y_jj U_j and stores (to the next block)": 0.0}
     for jb in range(nb):
         t4, t5, t6, t7 = (st[:, 4 + 4 * jb + k] for k in range(4))
         nxt = st[:, 4 + 4 * (jb + 1)] if jb + 1 < nb and 4 + 4 * (jb + 1) < CSLOT - 1 else st[:, CSLOT - 1]
         live = t4 > 0
-        acc["block tops and pairs with earlier blocks"] += np.where(live, t5 - t4, 0)
-        acc["diagonal block and its inverse"] += np.where(live, t6 - t5, 0)
+        acc["block tops, S0 products"] += np.where(live, t5 - t4, 0)
+        acc["pairs with earlier blocks"] += np.where(live, t6 - t5, 0)
         acc["U_j"] += np.where(live, t7 - t6, 0)
-        acc["O_j stores (to the next block)"] += np.where(live & (nxt > 0), nxt - t7, 0)
+        acc["Y_jj U_j and stores (to the next block)"] += np.where(live & (nxt > 0), nxt - t7, 0)
     rows.update(acc)
     print(f"workload {w.name} ({args.shape}): B={w.B} T={w.T} Hk={w.Hk} Hv={w.Hv} dk={w.dk} dv={w.dv}; "
           f"{st.shape[0]} workgroups, {nb} blocks of 32 slots; clocks of the last launch")
