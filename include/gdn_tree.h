@@ -179,8 +179,9 @@ int gdn_tree_verify_noalloc(const gdn_dims* dims, const void* meta, const void* 
  * MFMA as hi/lo three-product splits (about 16 significant bits), the
  * diagonal-block inverses on fp32 MFMA, features in fp32.  Arguments,
  * layouts, outputs and errors are those of gdn_tree_verify (any supported
- * dk, dv and T).  Needs a workspace of B T (C + Hv dv) 4 bytes, cached per
- * (device, stream) like gdn_tree_verify's above 128 slots.  Its cost does not
+ * dk, dv and T).  Needs a workspace of about B (T (C + Hv dv) + 1024 n (2 Hv +
+ * (n - 1) Hk)) 4 bytes, n = ceil(T / 32), cached per (device, stream) like
+ * gdn_tree_verify's above 128 slots.  Its cost does not
  * grow with the depth of the tree, while gdn_tree_verify's grows with the sum
  * of the path lengths. */
 int gdn_tree_verify_chunked(const gdn_dims* dims, const void* meta, const void* q, const void* k,

@@ -12,9 +12,9 @@
 // X is strictly lower triangular (ancestors come first), so U follows from a
 // forward substitution over sub-blocks of B_c = 32 positions (Eq. 13):
 //     U_j = (I + X_jj)^-1 (R_j - sum_{c<j} X_jc U_c),
-// where the inverse of each unit lower-triangular diagonal block is the
-// product (I - N)(I + N^2)(I + N^4)(I + N^8)(I + N^16), N = X_jj (N^32 = 0),
-// formed by repeated squaring.
+// where the inverse of each 16 x 16 tile on the diagonal is the product
+// (I - N)(I + N^2)(I + N^4)(I + N^8), N the tile of X_jj (N^16 = 0), formed by
+// repeated squaring, and the tile below them is -V11 X10 V00 (V the inverses).
 //
 // Three launches:
 //   features           (gdn_large.hip) fp32 rows F[B][T][C]
@@ -41,11 +41,14 @@
 // group m are rows 4 m + e of the block's first tile, slots e >= 4 rows 4 m + e
 // of its second; the A operand is laid out in the same order (slot_col).
 //
-// What bounds it and why this form: one workgroup per head that formed the Gram
-// blocks and the inverse itself ran 28 pairs and 8 inverses one after the other
-// with 3 to 7 barriers each, one workgroup per CU (150 KB): 8 chains of 256
-// slots, 16 / 48 heads of 128, took 367 us, hardly any of it in the products.
-// CHUNK_FIGURES
+// What bounds it and why this form: one workgroup per head that formed the
+// Gram blocks and the inverse itself ran 28 pairs and 8 inverses one after the
+// other with 3 to 7 barriers each, one workgroup per CU (150 KB): 8 chains of
+// 256 slots, 16 / 48 heads of 128, took 367 us, hardly any of it in the
+// products.  Now 47 us (Gram) + 100 us (cascade), two workgroups per CU, bound
+// by bytes (Gram 100 MB, cascade 310 MB) and the latency of a block's loads: a
+// register spilled while loads are in flight waits for all of them (7 in the
+// cascade: 120 us), and so does a branch around a load or store.
 #include <math.h>
 
 #include "gdn_pull.h"
