@@ -8,6 +8,7 @@ exceptions.  There is no fallback: if the library is missing the calls raise.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -92,6 +93,7 @@ def _check(rc: int) -> None:
         raise GdnError(rc, last_error())
 
 
+@functools.lru_cache(maxsize=64)
 def meta_bytes(B: int, T: int) -> int:
     return int(lib().gdn_tree_meta_bytes(B, T))
 
@@ -99,7 +101,13 @@ def meta_bytes(B: int, T: int) -> int:
 # ---------------------------------------------------------------------------
 # tensor marshalling
 # ---------------------------------------------------------------------------
-def _ptr(t, shape, dtype, name, allow_none=False):
+# A step passes 20 tensors; their checks and the call bounded the small steps
+# (one sequence, up to 64 slots: 30 us per prepare + step, 12 to 22 us of it
+# kernels).  So a tensor that is right takes one expression, and only one that
+# is not goes through _reject, which finds what is wrong in a fixed order: 18 us
+# for 7 slots of a toy layer, 22 us (the kernels) for 16 and 64 slots.
+def _reject(t, shape, dtype, name, allow_none):
+    """Raises for a tensor that cannot be passed; its pointer otherwise."""
     import torch
     if t is None:
         if allow_none:
@@ -117,13 +125,29 @@ def _ptr(t, shape, dtype, name, allow_none=False):
         raise ValueError(f"{name}: must be contiguous")
     if t.data_ptr() % 16:
         raise ValueError(f"{name}: must be 16-byte aligned")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptrs(args):
+    """Device pointers of args, tuples (tensor, shape, dtype, name[, None allowed])."""
+    from torch import Tensor
+    out = []
+    for a in args:
+        t = a[0]
+        if isinstance(t, Tensor) and t.dtype is a[2] and t.shape == a[1] and t.is_cuda and t.is_contiguous():
+            p = t.data_ptr()
+            if not p & 15:
+                out.append(p)
+                continue
+        out.append(_reject(*a[:4], len(a) > 4))
+    return out
 
 
 def _stream(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:  # of the current device, without the Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _in_dtype(d: Dims):
@@ -135,10 +159,11 @@ def prepare(d: Dims, parent, meta, tree_status=None, stream=None) -> None:
     """gdn_tree_prepare: parent int32 [B][T] -> meta (uint8, meta_bytes) and
     tree_status int32 [B] (optional)."""
     import torch
-    _check(lib().gdn_tree_prepare(
-        ctypes.byref(d), _ptr(parent, (d.B, d.T), torch.int32, "parent"),
-        _ptr(meta, (meta_bytes(d.B, d.T),), torch.uint8, "meta"),
-        _ptr(tree_status, (d.B,), torch.int32, "tree_status", allow_none=True), _stream(stream)))
+    i32, B, T = torch.int32, d.B, d.T
+    fn = lib().gdn_tree_prepare
+    _check(fn(ctypes.byref(d), *_ptrs((
+        (parent, (B, T), i32, "parent"), (meta, (meta_bytes(B, T),), torch.uint8, "meta"),
+        (tree_status, (B,), i32, "tree_status", None))), _stream(stream)))
 
 
 def verify(d: Dims, meta, q, k, v, alpha, beta, conv_w, conv_state, S0, out, stream=None,
@@ -152,14 +177,13 @@ def verify(d: Dims, meta, q, k, v, alpha, beta, conv_w, conv_state, S0, out, str
         raise ValueError("chunked and noalloc are separate entry points")
     fn = (lib().gdn_tree_verify_chunked if chunked else
           lib().gdn_tree_verify_noalloc if noalloc else lib().gdn_tree_verify)
-    _check(fn(
-        ctypes.byref(d), _ptr(meta, (meta_bytes(d.B, d.T),), torch.uint8, "meta"),
-        _ptr(q, (d.B, d.T, d.Hk, d.dk), it, "q"), _ptr(k, (d.B, d.T, d.Hk, d.dk), it, "k"),
-        _ptr(v, (d.B, d.T, d.Hv, d.dv), it, "v"), _ptr(alpha, (d.B, d.T, d.Hv), it, "alpha"),
-        _ptr(beta, (d.B, d.T, d.Hv), it, "beta"), _ptr(conv_w, (d.C, 4), f32, "conv_w"),
-        _ptr(conv_state, (d.B, 3, d.C), f32, "conv_state"),
-        _ptr(S0, (d.B, d.Hv, d.dv, d.dk), f32, "S0"),
-        _ptr(out, (d.B, d.T, d.Hv, d.dv), f32, "out"), _stream(stream)))
+    B, T, Hk, Hv, dk, dv = d.B, d.T, d.Hk, d.Hv, d.dk, d.dv
+    C, qk, vs, gs = 2 * Hk * dk + Hv * dv, (B, T, Hk, dk), (B, T, Hv, dv), (B, T, Hv)
+    _check(fn(ctypes.byref(d), *_ptrs((
+        (meta, (meta_bytes(B, T),), torch.uint8, "meta"), (q, qk, it, "q"), (k, qk, it, "k"),
+        (v, vs, it, "v"), (alpha, gs, it, "alpha"), (beta, gs, it, "beta"),
+        (conv_w, (C, 4), f32, "conv_w"), (conv_state, (B, 3, C), f32, "conv_state"),
+        (S0, (B, Hv, dv, dk), f32, "S0"), (out, vs, f32, "out"))), _stream(stream)))
 
 
 def commit(d: Dims, meta, accepted, q, k, v, alpha, beta, conv_w, conv_state, S,
@@ -168,16 +192,15 @@ def commit(d: Dims, meta, accepted, q, k, v, alpha, beta, conv_w, conv_state, S,
     [B][3][C] for the accepted slot of each sequence."""
     import torch
     f32, it = torch.float32, _in_dtype(d)
-    _check(lib().gdn_tree_commit(
-        ctypes.byref(d), _ptr(meta, (meta_bytes(d.B, d.T),), torch.uint8, "meta"),
-        _ptr(accepted, (d.B,), torch.int32, "accepted"),
-        _ptr(q, (d.B, d.T, d.Hk, d.dk), it, "q"), _ptr(k, (d.B, d.T, d.Hk, d.dk), it, "k"),
-        _ptr(v, (d.B, d.T, d.Hv, d.dv), it, "v"), _ptr(alpha, (d.B, d.T, d.Hv), it, "alpha"),
-        _ptr(beta, (d.B, d.T, d.Hv), it, "beta"), _ptr(conv_w, (d.C, 4), f32, "conv_w"),
-        _ptr(conv_state, (d.B, 3, d.C), f32, "conv_state"),
-        _ptr(S, (d.B, d.Hv, d.dv, d.dk), f32, "S"),
-        _ptr(commit_status, (d.B,), torch.int32, "commit_status", allow_none=True),
-        _stream(stream)))
+    fn = lib().gdn_tree_commit
+    B, T, Hk, Hv, dk, dv = d.B, d.T, d.Hk, d.Hv, d.dk, d.dv
+    C, qk, gs = 2 * Hk * dk + Hv * dv, (B, T, Hk, dk), (B, T, Hv)
+    _check(fn(ctypes.byref(d), *_ptrs((
+        (meta, (meta_bytes(B, T),), torch.uint8, "meta"), (accepted, (B,), torch.int32, "accepted"),
+        (q, qk, it, "q"), (k, qk, it, "k"), (v, (B, T, Hv, dv), it, "v"), (alpha, gs, it, "alpha"),
+        (beta, gs, it, "beta"), (conv_w, (C, 4), f32, "conv_w"),
+        (conv_state, (B, 3, C), f32, "conv_state"), (S, (B, Hv, dv, dk), f32, "S"),
+        (commit_status, (B,), torch.int32, "commit_status", None))), _stream(stream)))
 
 
 def step(d: Dims, prev_meta, prev_accepted, prev_q, prev_k, prev_v, prev_alpha, prev_beta,
@@ -187,23 +210,20 @@ def step(d: Dims, prev_meta, prev_accepted, prev_q, prev_k, prev_v, prev_alpha, 
     verification of the current tree; S is updated in place, the committed
     conv state goes to conv_state_out (conv_state is read-only)."""
     import torch
-    f32, it = torch.float32, _in_dtype(d)
-    mb = (meta_bytes(d.B, d.T),)
-    qk, vs, gs = (d.B, d.T, d.Hk, d.dk), (d.B, d.T, d.Hv, d.dv), (d.B, d.T, d.Hv)
-    _check(lib().gdn_tree_step(
-        ctypes.byref(d), _ptr(prev_meta, mb, torch.uint8, "prev_meta"),
-        _ptr(prev_accepted, (d.B,), torch.int32, "prev_accepted"),
-        _ptr(prev_q, qk, it, "prev_q"), _ptr(prev_k, qk, it, "prev_k"),
-        _ptr(prev_v, vs, it, "prev_v"), _ptr(prev_alpha, gs, it, "prev_alpha"),
-        _ptr(prev_beta, gs, it, "prev_beta"),
-        _ptr(commit_status, (d.B,), torch.int32, "commit_status", allow_none=True),
-        _ptr(meta, mb, torch.uint8, "meta"), _ptr(q, qk, it, "q"), _ptr(k, qk, it, "k"),
-        _ptr(v, vs, it, "v"), _ptr(alpha, gs, it, "alpha"), _ptr(beta, gs, it, "beta"),
-        _ptr(conv_w, (d.C, 4), f32, "conv_w"),
-        _ptr(conv_state, (d.B, 3, d.C), f32, "conv_state"),
-        _ptr(conv_state_out, (d.B, 3, d.C), f32, "conv_state_out"),
-        _ptr(S, (d.B, d.Hv, d.dv, d.dk), f32, "S"),
-        _ptr(out, (d.B, d.T, d.Hv, d.dv), f32, "out"), _stream(stream)))
+    f32, i32, u8, it = torch.float32, torch.int32, torch.uint8, _in_dtype(d)
+    fn = lib().gdn_tree_step
+    B, T, Hk, Hv, dk, dv = d.B, d.T, d.Hk, d.Hv, d.dk, d.dv
+    C, mb = 2 * Hk * dk + Hv * dv, (meta_bytes(B, T),)
+    qk, vs, gs, cs = (B, T, Hk, dk), (B, T, Hv, dv), (B, T, Hv), (B, 3, C)
+    _check(fn(ctypes.byref(d), *_ptrs((
+        (prev_meta, mb, u8, "prev_meta"), (prev_accepted, (B,), i32, "prev_accepted"),
+        (prev_q, qk, it, "prev_q"), (prev_k, qk, it, "prev_k"), (prev_v, vs, it, "prev_v"),
+        (prev_alpha, gs, it, "prev_alpha"), (prev_beta, gs, it, "prev_beta"),
+        (commit_status, (B,), i32, "commit_status", None), (meta, mb, u8, "meta"), (q, qk, it, "q"),
+        (k, qk, it, "k"), (v, vs, it, "v"), (alpha, gs, it, "alpha"), (beta, gs, it, "beta"),
+        (conv_w, (C, 4), f32, "conv_w"), (conv_state, cs, f32, "conv_state"),
+        (conv_state_out, cs, f32, "conv_state_out"), (S, (B, Hv, dv, dk), f32, "S"),
+        (out, vs, f32, "out"))), _stream(stream)))
 
 
 # ---------------------------------------------------------------------------
