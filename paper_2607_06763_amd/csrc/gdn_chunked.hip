@@ -45,10 +45,11 @@
 // Gram blocks and the inverse itself ran 28 pairs and 8 inverses one after the
 // other with 3 to 7 barriers each, one workgroup per CU (150 KB): 8 chains of
 // 256 slots, 16 / 48 heads of 128, took 367 us, hardly any of it in the
-// products.  Now 47 us (Gram) + 100 us (cascade), two workgroups per CU, bound
-// by bytes (Gram 100 MB, cascade 310 MB) and the latency of a block's loads: a
-// register spilled while loads are in flight waits for all of them (7 in the
-// cascade: 120 us), and so does a branch around a load or store.
+// products.  Now 47 us (Gram, 155 MB) + 100 us (cascade, 500 MB: the copy
+// rate; U comes back from the last-level cache for every later block), two
+// workgroups per CU.  Registers spilled while loads are in flight wait for
+// them one by one (7 in the cascade: 120 us), and so does a branch around a
+// load or store.
 #include <math.h>
 
 #include "gdn_pull.h"
@@ -60,7 +61,7 @@ constexpr int kBc = 32;       // positions per block (B_c)
 constexpr int kHMaxT = 512;   // tree slots supported
 constexpr int kHW = 8;        // ancestor words per node (512 / 64)
 constexpr int kLs = 36;       // row stride of the 32 x 32 matrices in LDS (floats)
-constexpr int kCG = 4;        // blocks c per workgroup of the Gram launch
+constexpr int kCG = 4;        // blocks c per workgroup of the Gram launch (2: 50 us instead of 47 at 8 x 256)
 constexpr int kCP = 2;        // earlier blocks per group of the cascade
 constexpr int kMaxNB = kHMaxT / kBc;
 constexpr int kUL = kBc + 8;  // bf16 row of an X or Y plane
