@@ -45,7 +45,7 @@
 // Gram blocks and the inverse itself ran 28 pairs and 8 inverses one after the
 // other with 3 to 7 barriers each, one workgroup per CU (150 KB): 8 chains of
 // 256 slots, 16 / 48 heads of 128, took 367 us, hardly any of it in the
-// products.  Now 47 us (Gram, 155 MB) + 100 us (cascade, 500 MB: the copy
+// products.  Now 42 us (Gram, 155 MB) + 100 us (cascade, 500 MB: the copy
 // rate; U comes back from the last-level cache for every later block), two
 // workgroups per CU.  Registers spilled while loads are in flight wait for
 // them one by one (7 in the cascade: 120 us), and so does a branch around a
@@ -192,11 +192,13 @@ __global__ __launch_bounds__(kHT, 6) void chunk_gram_kernel(ChunkParams p) {
   uint16_t* s_cl = s_ch + kBc * LKH;
   uint64_t* s_anc = reinterpret_cast<uint64_t*>(smem + SM::uni);  // [32][kHW]
 
-  const int g = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  const int g = blockIdx.x, b = blockIdx.z, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T = p.T, Hk = p.Hk, Hv = p.Hv, NB = (T + kBc - 1) / kBc;
+  // Key heads run fastest over the blocks: with 8 or 16 of them a head's groups
+  // share an XCD's L2 (42 us; groups fastest: 47).
   // block j has j / kCG + 1 groups of up to kCG blocks c <= j
-  int jb = 0, c0 = blockIdx.x;
+  int jb = 0, c0 = blockIdx.y;
   while (c0 > jb / kCG) {
     c0 -= jb / kCG + 1;
     ++jb;
@@ -440,7 +442,8 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
   // blocks: blocks u % 8 + 8 j of their group of 8 G, i.e. one XCD.
   const int T = p.T, Hk = p.Hk, Hv = p.Hv;
   const int G = Hv / Hk;
-  const int grp = blockIdx.x / (8 * G), rem = blockIdx.x % (8 * G);
+  const unsigned blk = blockIdx.y * gridDim.x + blockIdx.x;  // y above 1 only past 2^22 blocks
+  const int grp = blk / (8u * G), rem = blk % (8u * G);
   const int unit = 8 * grp + rem % 8;
   if (unit >= p.B * Hk) return;  // uniform
   const int b = unit / Hk, g = unit % Hk, h = g * G + rem / 8;
@@ -739,8 +742,11 @@ static int launch_chunk_t(const ChunkParams& p, hipStream_t stream) {
   const int NB = (p.T + kBc - 1) / kBc, G = p.Hv / p.Hk, units = p.B * p.Hk;
   int groups = 0;
   for (int j = 0; j < NB; ++j) groups += j / kCG + 1;
-  hipLaunchKernelGGL((chunk_gram_kernel<DK, TIn>), dim3(groups, p.Hk, p.B), dim3(kHT), SG::total, stream, p);
-  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), dim3((units + 7) / 8 * 8 * G), dim3(kHT), SM::total, stream, p);
+  hipLaunchKernelGGL((chunk_gram_kernel<DK, TIn>), dim3(p.Hk, groups, p.B), dim3(kHT), SG::total, stream, p);
+  // whole groups of 8 G blocks; rows of the grid keep its width below the limit
+  const int rows = (units + 7) / 8, wide = (1 << 19) / G > 0 ? (1 << 19) / G : 1;
+  const dim3 grid(unsigned(rows < wide ? rows : wide) * 8u * G, (rows + wide - 1) / wide);
+  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), grid, dim3(kHT), SM::total, stream, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(GDN_EHIP, "verify_chunked launch: %s", hipGetErrorString(e));
   return GDN_OK;
