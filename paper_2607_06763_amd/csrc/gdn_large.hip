@@ -637,9 +637,11 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     const int a = ord[2 * kLMaxT + (live ? j : 0)];
     row = row >= 0 && row < T ? row : 0;
     RowGate g = {0.0f, 0.0f, 0.0f, 0};
+    // the scale, and with it the mark, of the row that is loaded: an absent
+    // row's coefficient is 0, and 0 times inf would reach the whole tile
+    if (nval > 0) g.vs = p.Vs[(bt + row) * Hv + h];
     if (real) {
       const int nd = m_.order[bt + row];
-      g.vs = p.Vs[(bt + row) * Hv + h];
       const float la = __builtin_amdgcn_logf(ld(alpha, (bt + nd) * Hv + h));
       g.la = la < -512.0f ? -512.0f : la;  // a decay of 0 stays finite, 2^la is 0
       g.be = ld(beta, (bt + nd) * Hv + h);

@@ -78,3 +78,41 @@ def test_not_finite_reaches_only_descendants(G, orc, what, value):
         assert not np.isfinite(got[b, j, h]).all()
         keep[b, desc, h] = False
     np.testing.assert_array_equal(got[keep].view(np.int32), clean[keep].view(np.int32))
+
+
+def _stem_and_branch(T, anc, branch=2):
+    """Root and a stem, `anc` nodes in all, leaves of its last one, and last in
+    depth-first order a branch of `branch` nodes below the root: the leaves'
+    tiles walk a path whose last chunk has absent rows unless 16 divides anc."""
+    par = np.full(T, W.PAD, np.int32)
+    for i in range(T):
+        par[i] = W.ROOT if i == 0 else i - 1 if i < anc else anc - 1
+    for j in range(branch):
+        par[T - branch + j] = 0 if j == 0 else T - branch + j - 1
+    return par
+
+
+@pytest.mark.parametrize("anc", [1, 5, 15, 16, 17, 31, 40, 100])
+@pytest.mark.parametrize("back,value", [(0, float("inf")), (0, float("nan")), (1, float("-inf")), (1, float("nan"))])
+def test_not_finite_value_at_the_last_node(G, anc, back, value):
+    """A value that is not finite at the last node in depth-first order, or at
+    its parent: absent rows of a path chunk load that node's row."""
+    import torch
+    T = 150
+    w = W.make_random(9400 + anc, 1, T, 1, 2, 32, 64, "f32", parent=_stem_and_branch(T, anc)[None])
+    j = T - 1 - back
+    print(f"[gpu] v = {value} at slot {j}, {anc} ancestors of the other leaves", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    clean = dt.out.clone().cpu().numpy()
+    assert np.isfinite(clean).all()
+    dt.v[0, j, 1, 3] = value
+    dt.verify()
+    torch.cuda.synchronize()
+    got = dt.out.cpu().numpy()
+    assert not np.isfinite(got[0, j:, 1, 3]).any()
+    keep = np.ones(got.shape, bool)
+    keep[0, j:, 1] = False
+    np.testing.assert_array_equal(got[keep].view(np.int32), clean[keep].view(np.int32))
