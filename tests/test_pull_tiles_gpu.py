@@ -116,3 +116,29 @@ def test_not_finite_value_at_the_last_node(G, anc, back, value):
     keep = np.ones(got.shape, bool)
     keep[0, j:, 1] = False
     np.testing.assert_array_equal(got[keep].view(np.int32), clean[keep].view(np.int32))
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_not_finite_value_keeps_other_channels(G, value):
+    """A v~ row with one channel that is not finite: the other channels of the
+    nodes below it come from the value terms of all their path rows."""
+    import torch
+    T = 200
+    w = W.make_random(9500, 2, T, 1, 2, 32, 32, "f32", shuffle=True)
+    w.S0 = np.zeros_like(w.S0)
+    print(f"[gpu] v = {value} in one channel of every fifth slot", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    clean = dt.out.clone().cpu().numpy()
+    dt.v[:, ::5, :, 3] = value
+    dt.verify()
+    torch.cuda.synchronize()
+    got = dt.out.cpu().numpy()
+    assert not np.isfinite(got[..., 3]).all()
+    other = np.arange(32) != 3
+    # the scale of such a row may be another power of two: fp16 values below
+    # 2^-14 of its largest round differently, by 2^-25 of it
+    err = np.max(np.abs(got[..., other] - clean[..., other])) / np.max(np.abs(clean))
+    assert err <= 1e-5
