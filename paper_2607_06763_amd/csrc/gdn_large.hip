@@ -866,12 +866,16 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       for (int e = 0; e < 4; ++e) mm[e] = c[e] * __builtin_amdgcn_exp2f(lr[e]) * vs[e];
       return mm;
     };
-    auto largest = [](f32x4 a) { return fmaxf(fmaxf(fabsf(a[0]), fabsf(a[1])), fmaxf(fabsf(a[2]), fabsf(a[3]))); };
-    // acc = f acc + V^T (scl mm) over the chunk, whose v~ rows are in vf
-    auto values = [&](const int16_t* lst, f32x4 mm, float scl, float f, bool marked, auto ahead) {
+    // acc (+)= V^T mm over the chunk, whose v~ rows are in vf.  In fp32: the
+    // coefficients of a path differ without bound, and a small one counts in
+    // the channels where the rows of the large ones are 0.  As fp16 hi + lo
+    // under one scale per node (2 products instead of 4) the launch took 310
+    // instead of 335 us at 32 x 512 (with the commit), 48 instead of 54 at 16
+    // x 250, and lost what was below 2^-25 of the node's largest.  The rate of
+    // the fp32 products is what they cost: 2 or 4 channel tiles in turn took as
+    // long.
+    auto values = [&](const int16_t* lst, f32x4 mm, bool marked, auto ahead) {
       const int ln = opaque(lane), l16 = ln & 15, m = ln >> 4;
-      f16x4 h0, l0;
-      split4(mm, scl, h0, l0);
       if (marked) vf.keep_finite();
       vf.store(buf, ln);
       ahead();
@@ -879,8 +883,9 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
 #pragma unroll
       for (int t = 0; t < NV; ++t) {
         const f16x4 a = VF::columns(buf, t, l16, m);
-        acc[t] = mfma_h16(a, l0, lst ? acc[t] * f : z4);
-        acc[t] = mfma_h16(a, h0, acc[t]);
+        if (!lst) acc[t] = z4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t] = mfma_f((float)a[e], mm[e], acc[t]);
       }
       wave_lds_order();
       if (marked) {
@@ -890,8 +895,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
         for (int j = 0; j < kLTile; ++j) {
           const int i = index(lst, j), e = j >> 2;
           const RowGate g = s_g[i];
-          const float cj =
-              scl * __shfl(e == 0 ? mm[0] : (e == 1 ? mm[1] : (e == 2 ? mm[2] : mm[3])), l16 + 16 * (j & 3));
+          const float cj = __shfl(e == 0 ? mm[0] : (e == 1 ? mm[1] : (e == 2 ? mm[2] : mm[3])), l16 + 16 * (j & 3));
           if (i <= n && n < g.end && g.vs < 0.0f) {
             const _Float16* v = Fv + size_t(s_row[i]) * C + 4 * m;
 #pragma unroll
@@ -908,7 +912,6 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // The first two chunks' values follow both solutions: x and the solver's
     // registers are then not live together with acc (128 registers allow two
     // workgroups per CU).
-    float mrun, inv;  // largest value coefficient, power of two acc is divided by
     auto none = [] {};
     {
       float va = 0.0f, vb = 0.0f;
@@ -920,13 +923,10 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
         mb = solve(path, vb, [&] { load_v(nullptr); });
       else
         load_v(nullptr);
-      mrun = cross_max(fmaxf(largest(ma), largest(mb)));
-      float scl;
-      row_scale(mrun, scl, inv);
-      values(nullptr, ma, scl, 0.0f, __any(va < 0.0f), [&] {
+      values(nullptr, ma, __any(va < 0.0f), [&] {
         if (near < kLMaxT) load_v(path);
       });
-      if (near < kLMaxT) values(path, mb, scl, 1.0f, __any(vb < 0.0f), none);
+      if (near < kLMaxT) values(path, mb, __any(vb < 0.0f), none);
     }
     if (path[0] < kLMaxT && path[0] > 0) {
       // more than 16 ancestors (the 16th is not the root): 16 at a time,
@@ -947,17 +947,13 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
         float vb = 0.0f;
         const f32x4 mb = solve(list, vb, none);
         load_v(list);  // not ahead: acc is live here
-        mrun = fmaxf(mrun, cross_max(largest(mb)));
-        float scl;
-        const float pinv = inv;
-        row_scale(mrun, scl, inv);
-        values(list, mb, scl, pinv * scl, __any(vb < 0.0f), none);
+        values(list, mb, __any(vb < 0.0f), none);
       }
     }
     // ---- O^T = S0 (r X)^T + acc.  r x enters as fp16 hi + lo: with fp16
     // features the key dims are short, and an x rounded once to 11 bits cost
     // up to 3e-4 of max|o| on 16-dim heads.
-    const float r = __builtin_amdgcn_exp2f(lw), ainv = p.scale * inv;
+    const float r = __builtin_amdgcn_exp2f(lw);
     f16x8 xh[KB], xl[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
@@ -978,8 +974,8 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
         d = mfma_h(a, xh[kb], d);
       }
       const float4 si = *reinterpret_cast<const float4*>(s_inv + 16 * t + 4 * m);
-      const float4 o = make_float4(fmaf(d[0], si.x, acc[t][0] * ainv), fmaf(d[1], si.y, acc[t][1] * ainv),
-                                   fmaf(d[2], si.z, acc[t][2] * ainv), fmaf(d[3], si.w, acc[t][3] * ainv));
+      const float4 o = make_float4(fmaf(d[0], si.x, acc[t][0] * p.scale), fmaf(d[1], si.y, acc[t][1] * p.scale),
+                                   fmaf(d[2], si.z, acc[t][2] * p.scale), fmaf(d[3], si.w, acc[t][3] * p.scale));
       if (n < T) *reinterpret_cast<float4*>(dst + 16 * t) = n < nval ? o : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }

@@ -12,7 +12,8 @@
 // substitution per chunk of path nodes,
 //     s = K_c x,   (I + N) c = beta s  with N_tt' = beta_t k_t.k_t' (t above t'),
 //     x -= K_c^T c,   acc += V_c^T (r c),
-// with the 16 nodes as matrix columns.
+// with the 16 nodes as matrix columns.  s and x take their fp32 operand as fp16
+// hi + lo, acc in fp32.
 //
 // Layouts (v_mfma_f32_16x16x32_f16).  Lane (l16, m) = (lane % 16, lane / 16)
 // of an accumulator holds rows 4 m + e (e < 4) of column l16.  An accumulator
@@ -36,7 +37,8 @@ __device__ __forceinline__ f16x8 cat(f16x4 a, f16x4 b) { return __builtin_shuffl
 __device__ __forceinline__ f16x4 to_h4(f32x4 x) {
   return f16x4{(_Float16)x[0], (_Float16)x[1], (_Float16)x[2], (_Float16)x[3]};
 }
-// x y = hi + lo + O(2^-22 |x y|), with the product not rounded in between.
+// x y = hi + lo, off by at most 2^-22 |x y| + 2^-25 (the last fp16 place above
+// 0), with the product not rounded in between.
 // For a split of x alone y is a 1.0 that the compiler cannot see (one_f):
 // the remainder is then one mixed-precision FMA per value.
 __device__ __forceinline__ void split4(f32x4 x, float y, f16x4& hi, f16x4& lo) {
@@ -74,15 +76,6 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
-// Largest value over the four lanes l16, l16 + 16, + 32, + 48.
-__device__ __forceinline__ float cross_max(float v) {
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  u2 a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-  v = fmaxf(__uint_as_float(a.x), __uint_as_float(a.y));
-  a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-  return fmaxf(__uint_as_float(a.x), __uint_as_float(a.y));
 }
 
 // x, or 0 when it is not finite

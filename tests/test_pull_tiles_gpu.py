@@ -142,3 +142,32 @@ def test_not_finite_value_keeps_other_channels(G, value):
     # 2^-14 of its largest round differently, by 2^-25 of it
     err = np.max(np.abs(got[..., other] - clean[..., other])) / np.max(np.abs(clean))
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("ratio", [1e4, 1e8, 1e14])
+def test_small_values_beside_large_ones(G, orc, ratio):
+    """Path rows whose values differ by `ratio`, in different channels: the
+    small ones keep the accuracy of the features (bar of the other tests, per
+    channel range)."""
+    import torch
+    T = 180
+    rng = np.random.default_rng(9600)
+    w = W.make_random(9600, 2, T, 1, 2, 64, 32, "f32", parent=np.stack([_broom(T, T, 40), W.random_tree(rng, T)]))
+    w.S0 = np.zeros_like(w.S0)
+    w.conv_w = np.zeros_like(w.conv_w)
+    w.conv_w[:, 3] = 1.0  # no taps across nodes
+    dep = orc.prepare(w.parent)["depth"]
+    v = np.abs(w.v) + 0.5
+    v[..., :16] *= np.float32(ratio) * (dep % 2 == 1)[..., None, None]
+    v[..., 16:] *= (dep % 2 == 0)[..., None, None]
+    w.v = v.astype(np.float32)
+    print(f"[gpu] values that differ by {ratio:g}", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    ref, got = orc.verify(w), dt.out.cpu().numpy()
+    for ch in (slice(0, 16), slice(16, 32)):
+        err = np.max(np.abs(got[..., ch] - ref[..., ch])) / np.max(np.abs(ref[..., ch]))
+        print(f"[gpu]   channels {ch.start}.. err {err:.3e}", flush=True)
+        assert err <= O_TOL
