@@ -580,7 +580,7 @@ struct RowStage {
 
 // Gates of a node for one value head
 struct RowGate {
-  float be, la, vs;  // beta, log2 alpha, inverse v~ row scale (sign: see LargeParams)
+  float be, al, vs;  // beta, alpha, inverse v~ row scale (sign: see LargeParams)
   int end;           // end of the subtree, 0 past the nodes
 };
 
@@ -651,8 +651,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     if (nval > 0) g.vs = p.Vs[(bt + row) * Hv + h];
     if (real) {
       const int nd = m_.order[bt + row];
-      const float la = __builtin_amdgcn_logf(ld(alpha, (bt + nd) * Hv + h));
-      g.la = la < -512.0f ? -512.0f : la;  // a decay of 0 stays finite, 2^la is 0
+      g.al = ld(alpha, (bt + nd) * Hv + h);
       g.be = ld(beta, (bt + nd) * Hv + h);
       g.end = end;
     }
@@ -712,8 +711,6 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
   unsigned char* buf = smem + SM::plane + wave * SM::chunk;
   float* z = s_solve + 64 * wave;
   int16_t* list = s_list + kLTile * wave;
-  const _Float16 one = (_Float16)1.0f;
-  const f16x8 ones = {one, one, one, one, one, one, one, one};
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
   for (int n0 = kLTile * wave; n0 < T; n0 += kLT / 64 * kLTile) {
     // lane roles from values that the compiler cannot see through: addresses
@@ -760,8 +757,8 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       for (int t = 0; t < NX; ++t) qc[t] = KF::slots(buf, t, l16, m);
       wave_lds_order();
     }
-    float lw = 0.0f;  // log2 of the decay of the rows walked
-    // The substitution over one chunk of path nodes: x and lw move up by the
+    float rw = 1.0f;  // decay of the rows walked
+    // The substitution over one chunk of path nodes: x and rw move up by the
     // chunk; returns the value coefficients r c / (v~ row scale) of the
     // accumulator rows.  kf: the chunk's k~ rows on entry; once they are in
     // LDS, ahead() issues later loads.  vmin: below 0 if a v~ row of this
@@ -820,7 +817,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
         }
       }
       // ---- gates of accumulator rows e = 0 .. 3 (rows without a node: end 0)
-      f32x4 bm, la, vs;
+      f32x4 bm, al, vs;
       int ie[4];
       RowGate ge[4];
 #pragma unroll
@@ -829,13 +826,13 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
         ge[e] = s_g[ie[e]];
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(ge[e].be), "+v"(ge[e].la), "+v"(ge[e].vs));  // loaded, not branched around
+      for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(ge[e].be), "+v"(ge[e].al), "+v"(ge[e].vs));  // loaded, not branched around
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const RowGate g = ge[e];
         const bool on = ie[e] <= n && n < g.end;
         bm[e] = on ? ((badk >> (4 * m + e)) & 1 ? __builtin_nanf("") : g.be) : 0.0f;
-        la[e] = on ? g.la : 0.0f;
+        al[e] = on ? g.al : 1.0f;
         vs[e] = fabsf(g.vs);
         vmin = fminf(vmin, g.vs);
       }
@@ -843,15 +840,11 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       // 4; row il is the block's row i (a chain, or an absent row, beta 0)
       const bool up = (l16 >> 2) < m && (!own || n0 + 4 * (l16 & 3) + m < gl.end);
       const float di = block_inverse(z, up ? finite(gl.be) * diag_entry(gm, l16) : 0.0f, l16, m);
-      f16x4 h0, l0;
-      split4(la, y1, h0, l0);
-      const f16x4 an = above_rows(l16, m, own ? gl.end - n0 : kLTile);
-      const f32x4 w0 = {lw, lw, lw, lw};
-      const f32x4 lr = mfma_h(cat(an, an), cat(h0, l0), w0);
-      lw = mfma_h(ones, cat(h0, l0), w0)[0];
+      const f32x4 lr = decays(al, rw, m);
       const f32x4 c = substitute(s, gm, di, bm, l16);
       __builtin_amdgcn_sched_barrier(0);
       // ---- x -= K^T c
+      f16x4 h0, l0;
       split4(-c, y1, h0, l0);
 #pragma unroll
       for (int t = 0; t < NX; ++t) {
@@ -863,7 +856,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       wave_lds_order();
       f32x4 mm;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) mm[e] = c[e] * __builtin_amdgcn_exp2f(lr[e]) * vs[e];
+      for (int e = 0; e < 4; ++e) mm[e] = c[e] * lr[e] * vs[e];
       return mm;
     };
     // acc (+)= V^T mm over the chunk, whose v~ rows are in vf.  In fp32: the
@@ -953,13 +946,12 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // ---- O^T = S0 (r X)^T + acc.  r x enters as fp16 hi + lo: with fp16
     // features the key dims are short, and an x rounded once to 11 bits cost
     // up to 3e-4 of max|o| on 16-dim heads.
-    const float r = __builtin_amdgcn_exp2f(lw);
     f16x8 xh[KB], xl[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
       f16x4 h0, l0, h1 = {0, 0, 0, 0}, l1 = {0, 0, 0, 0};
-      split4(x[2 * kb], r, h0, l0);
-      if constexpr (NX > 1) split4(x[2 * kb + 1], r, h1, l1);
+      split4(x[2 * kb], rw, h0, l0);
+      if constexpr (NX > 1) split4(x[2 * kb + 1], rw, h1, l1);
       xh[kb] = cat(h0, h1);
       xl[kb] = cat(l0, l1);
     }

@@ -125,14 +125,25 @@ __device__ __forceinline__ f32x4 substitute(f32x4 s, f32x4 g, float dinv, f32x4 
   return c;
 }
 
-// 1.0 where operand row l16 is above column rows rho = 4 m + e: tau(l16) <
-// tau < end (end: end of the row's subtree in the chunk; 16 in a chain).
-__device__ __forceinline__ f16x4 above_rows(int l16, int m, int end) {
-  f16x4 a;
+// Decay from each accumulator row of a chunk down to the column's node: rw
+// times the alphas of the rows below it (al: alpha on the column's path, else
+// 1).  rw moves up by the chunk.  Products, not sums of logarithms: alpha may
+// be 0 or negative.
+__device__ __forceinline__ f32x4 decays(f32x4 al, float& rw, int m) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  f32x4 lr;
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    a[e] = (4 * e + m > tau_of(l16) && 4 * e + m < end) ? (_Float16)1.0f : (_Float16)0.0f;
-  return a;
+  for (int e = 3; e >= 0; --e) {  // rows tau = 4 e + m: the four lane groups hold four consecutive ones
+    const unsigned a = __float_as_uint(al[e]);
+    u2 w = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a, a, false, false));
+    const float odd = __uint_as_float(w.y);  // of this pair of groups
+    const unsigned pair = __float_as_uint(__uint_as_float(w.x) * odd);
+    w = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(pair, pair, false, false));
+    const float upper = __uint_as_float(w.y);  // groups 2 and 3
+    lr[e] = rw * ((m & 1 ? 1.0f : odd) * (m < 2 ? upper : 1.0f));
+    rw *= __uint_as_float(w.x) * upper;
+  }
+  return lr;
 }
 
 // Column of an fp16 state plane that holds channel k: within 32 channels the

@@ -171,3 +171,21 @@ def test_small_values_beside_large_ones(G, orc, ratio):
         err = np.max(np.abs(got[..., ch] - ref[..., ch])) / np.max(np.abs(ref[..., ch]))
         print(f"[gpu]   channels {ch.start}.. err {err:.3e}", flush=True)
         assert err <= O_TOL
+
+
+@pytest.mark.parametrize("T,n", [(128, 120), (200, 180)])
+def test_decays_of_either_sign(G, orc, T, n):
+    """Decays below and at zero, on both sides of the on-chip size."""
+    import torch
+    w = W.make_random(9700, 2, T, 1, 2, 64, 32, "f32", n_valid=[n, T], shuffle=True)
+    w.alpha = (w.alpha * np.random.default_rng(9700).choice([-1.0, 0.0, 1.0], w.alpha.shape, p=[0.5, 0.1, 0.4])).astype(
+        np.float32)
+    print(f"[gpu] decays of either sign T={T}", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    ref = orc.verify(w)
+    err = np.max(np.abs(dt.out.cpu().numpy() - ref)) / np.max(np.abs(ref))
+    print(f"[gpu]   err {err:.3e}", flush=True)
+    assert err <= O_TOL
