@@ -925,7 +925,8 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       // more than 16 ancestors (the 16th is not the root): 16 at a time,
       // found as the nodes before the tile whose subtree reaches past its
       // first node
-      const int np = m_.pdep[bt + s_row[n0]];
+      const int dep = m_.pdep[bt + s_row[n0]];
+      const int np = dep < nval ? dep : nval;  // corrupt metadata: the loop ends all the same
       for (int base = np - 2 * kLTile; base > -kLTile; base -= kLTile) {
         if (lane < kLTile) list[lane] = int16_t(kLMaxT);
         wave_lds_order();

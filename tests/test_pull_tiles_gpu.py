@@ -189,3 +189,25 @@ def test_decays_of_either_sign(G, orc, T, n):
     err = np.max(np.abs(dt.out.cpu().numpy() - ref)) / np.max(np.abs(ref))
     print(f"[gpu]   err {err:.3e}", flush=True)
     assert err <= O_TOL
+
+
+def test_wild_depth_in_the_metadata(G):
+    """Depths by position that no tree has end the walk over deeper ancestors
+    after at most T / 16 chunks; other tiles and sequences do not see them."""
+    import torch
+    T = 160
+    w = W.make_random(9800, 2, T, 1, 2, 32, 32, "f32", parent=np.stack([W.chain_tree(T)] * 2))
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    clean = dt.out.clone().cpu().numpy()
+    off = G.meta_layout(2, T)["pdep"]
+    pdep = dt.meta[off:off + 4 * 2 * T].view(torch.int32).view(2, T)
+    pdep[0, 144:] = 2 ** 31 - 1  # the last tile of the first sequence (a chain's depth-first order is its own)
+    print("[gpu] wild depths in the last tile", flush=True)
+    dt.verify()
+    torch.cuda.synchronize()
+    got = dt.out.cpu().numpy()
+    np.testing.assert_array_equal(got[0, :144].view(np.int32), clean[0, :144].view(np.int32))
+    np.testing.assert_array_equal(got[1].view(np.int32), clean[1].view(np.int32))
