@@ -533,12 +533,13 @@ struct RowStage {
   static constexpr int PPR = D / 8;              // 16-byte pieces per row
   static constexpr int NI = (kLTile * PPR + 63) / 64;
   f16x8 st[NI];
-  // rowoff: in lane rho (and rho + 16, ...), byte offset of row rho
-  __device__ __forceinline__ void load(const _Float16* base, int rowoff, int lane) {
+  // rowoff: in lane rho (and rho + 16, ...), byte offset of row rho (rows of
+  // one sequence span less than 4 GB)
+  __device__ __forceinline__ void load(const _Float16* base, uint32_t rowoff, int lane) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int rho = (64 / PPR * i + lane / PPR) & (kLTile - 1);
-      const int off = __builtin_amdgcn_ds_bpermute(4 * rho, rowoff) + 16 * (lane % PPR);
+      const uint32_t off = uint32_t(__builtin_amdgcn_ds_bpermute(4 * rho, int(rowoff))) + 16u * (lane % PPR);
       st[i] = *reinterpret_cast<const f16x8*>(reinterpret_cast<const char*>(base) + off);
     }
   }
@@ -741,13 +742,13 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     const int16_t* path = s_path + n0;
     const int near = path[kLTile - 1];  // parent of the tile's first node
     auto row_off = [&](const int16_t* lst) {  // of operand row l16
-      return int(s_row[index(lst, tau_of(opaque(lane) & 15))]) * int(2 * C);
+      return uint32_t(s_row[index(lst, tau_of(opaque(lane) & 15))]) * uint32_t(2 * C);
     };
     auto load_k = [&](const int16_t* lst) { kf.load(Fk, row_off(lst), opaque(lane)); };
     auto load_v = [&](const int16_t* lst) { vf.load(Fv, row_off(lst), opaque(lane)); };
     {
       KF qs;
-      qs.load(Fb + g * DK, int(s_row[n]) * int(2 * C), lane);
+      qs.load(Fb + g * DK, uint32_t(s_row[n]) * uint32_t(2 * C), lane);
       load_k(nullptr);
       qs.store(buf, opaque(lane));
       wave_lds_order();

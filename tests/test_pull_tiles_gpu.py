@@ -211,3 +211,39 @@ def test_wild_depth_in_the_metadata(G):
     got = dt.out.cpu().numpy()
     np.testing.assert_array_equal(got[0, :144].view(np.int32), clean[0, :144].view(np.int32))
     np.testing.assert_array_equal(got[1].view(np.int32), clean[1].view(np.int32))
+
+
+def test_rows_past_2_gb(G):
+    """16640 value heads of 128 at 512 slots: the feature rows of a sequence
+    span more than 2^31 bytes.  The last heads equal the same heads alone."""
+    import torch
+    T, dk, dv, Hv, keep = 512, 16, 128, 16640, 2
+    C = 2 * dk + Hv * dv
+    assert (T - 1) * 2 * C > 2 ** 31
+    print(f"[gpu] rows past 2 GB: {Hv} value heads", flush=True)
+    w = W.make_random(9900, 1, T, 1, keep, dk, dv, "bf16", parent=_broom(T, T, 20)[None])
+    small = G.DeviceTree(w)
+    small.prepare()
+    small.verify()
+    d = G.make_dims(1, T, 1, Hv, dk, dv, "bf16")
+
+    def widen(x, dim, fill):
+        """x as the last entries along dim of a larger tensor."""
+        shape = list(x.shape)
+        shape[dim] = C if x.shape[dim] == w.C else Hv
+        y = torch.full(shape, fill, dtype=x.dtype, device=x.device)
+        n = x.shape[dim]
+        if n == w.C:  # q and k channels come first
+            y.narrow(dim, 0, 2 * dk).copy_(x.narrow(dim, 0, 2 * dk))
+            y.narrow(dim, C - keep * dv, keep * dv).copy_(x.narrow(dim, 2 * dk, keep * dv))
+        else:
+            y.narrow(dim, Hv - n, n).copy_(x)
+        return y
+
+    out = torch.empty((1, T, Hv, dv), device="cuda")
+    G.verify(d, small.meta, small.q, small.k, widen(small.v, 2, 0.0), widen(small.alpha, 2, 0.5),
+             widen(small.beta, 2, 0.5), widen(small.conv_w, 0, 0.0), widen(small.conv_state, 2, 0.0),
+             widen(small.S0, 1, 0.0), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :, Hv - keep:].contiguous().view(torch.int32), small.out.view(torch.int32))
+    assert not out[:, :, :Hv - keep].any()
