@@ -93,7 +93,7 @@ def _check(rc: int) -> None:
         raise GdnError(rc, last_error())
 
 
-@functools.lru_cache(maxsize=64)
+@functools.lru_cache(maxsize=64, typed=True)  # 2.0 is refused, also after 2
 def meta_bytes(B: int, T: int) -> int:
     return int(lib().gdn_tree_meta_bytes(B, T))
 
