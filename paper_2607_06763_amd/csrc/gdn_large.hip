@@ -639,6 +639,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
   }
   // ---- order and this head's gates by depth-first index
   const int16_t* ord = p.ord + size_t(b) * 3 * kLMaxT;
+  bool grows = false;
   for (int j = tid; j <= kLMaxT; j += kLT) {
     const bool real = j < nval;
     int row = nval > 0 ? ord[real ? j : nval - 1] : 0;  // past the nodes: the last one's row
@@ -655,6 +656,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       g.al = ld(alpha, (bt + nd) * Hv + h);
       g.be = ld(beta, (bt + nd) * Hv + h);
       g.end = end;
+      grows = grows || g.be < 0.0f || g.be > 2.0f;
     }
     s_g[j] = g;
     s_row[j] = int16_t(row);
@@ -706,7 +708,12 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     for (int i = tid; i < DV * (32 - DK); i += kLT)
       s_plane[(i / (32 - DK)) * KP + plane_col(DK + i % (32 - DK))] = (_Float16)0.0f;
   }
-  __syncthreads();
+  // q~, and with it x and c, is taken times xunit, so that the fp16 hi + lo that
+  // the products take of x and c end at 2^-38 of |q~| = 1, not at 2^-25.  For
+  // beta in [0, 2] |x| does not grow and 2^13 leaves c a factor of 4 below
+  // fp16's largest; with any other beta it may, and x has all of fp16's range.
+  const bool grown = __builtin_amdgcn_readfirstlane(__syncthreads_or(grows)) != 0;
+  const float xunit = grown ? 1.0f : 0x1p13f;
 
   // ---- tiles of 16 nodes, one wave each: no barrier below
   unsigned char* buf = smem + SM::plane + wave * SM::chunk;
@@ -736,9 +743,9 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // chunk's k~ while one is solved, vf the own v~ rows while the second is.
     KF kf;
     VF vf;
-    f16x8 qf[KB];   // q~ of column l16, channel order
+    f16x8 qf[KB];   // q~ of column l16 times xunit, channel order
     f16x4 qc[NX];   // and accumulator order
-    f32x4 x[NX], acc[NV];
+    f32x4 x[NX], acc[NV];  // x times xunit
     const int16_t* path = s_path + n0;
     const int near = path[kLTile - 1];  // parent of the tile's first node
     auto row_off = [&](const int16_t* lst) {  // of operand row l16
@@ -750,6 +757,8 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       KF qs;
       qs.load(Fb + g * DK, uint32_t(s_row[n]) * uint32_t(2 * C), lane);
       load_k(nullptr);
+#pragma unroll
+      for (int i = 0; i < KF::NI; ++i) qs.st[i] *= (_Float16)xunit;
       qs.store(buf, opaque(lane));
       wave_lds_order();
 #pragma unroll
@@ -758,7 +767,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       for (int t = 0; t < NX; ++t) qc[t] = KF::slots(buf, t, l16, m);
       wave_lds_order();
     }
-    float rw = 1.0f;  // decay of the rows walked
+    float rw = grown ? 1.0f : 0x1p-13f;  // decay of the rows walked, over xunit
     // The substitution over one chunk of path nodes: x and rw move up by the
     // chunk; returns the value coefficients r c / (v~ row scale) of the
     // accumulator rows.  kf: the chunk's k~ rows on entry; once they are in

@@ -13,7 +13,7 @@
 //     s = K_c x,   (I + N) c = beta s  with N_tt' = beta_t k_t.k_t' (t above t'),
 //     x -= K_c^T c,   acc += V_c^T (r c),
 // with the 16 nodes as matrix columns.  s and x take their fp32 operand as fp16
-// hi + lo, acc in fp32.
+// hi + lo, scaled (split4 says how far off that is), acc in fp32.
 //
 // Layouts (v_mfma_f32_16x16x32_f16).  Lane (l16, m) = (lane % 16, lane / 16)
 // of an accumulator holds rows 4 m + e (e < 4) of column l16.  An accumulator

@@ -247,3 +247,55 @@ def test_rows_past_2_gb(G):
     torch.cuda.synchronize()
     assert torch.equal(out[:, :, Hv - keep:].contiguous().view(torch.int32), small.out.view(torch.int32))
     assert not out[:, :, :Hv - keep].any()
+
+
+@pytest.mark.parametrize("beta", [1e-3, 1e-5, 1e-7])
+def test_small_updates_of_the_query(G, orc, beta):
+    """Features that fp16 holds exactly (one entry of 1, or four of 1/2): what
+    is left is the walk's own error.  A weak write at node 100 gives q~ entries
+    of beta / 8 that only the key of node 50, two chunks further up, reads."""
+    import torch
+    T, hot = 140, 30.0  # SiLU(30) = 30
+    w = W.make_random(9650, 1, T, 1, 1, 32, 16, "f32", parent=W.chain_tree(T)[None])
+    w.conv_w = np.zeros_like(w.conv_w)
+    w.conv_w[:, 3] = 1.0  # no taps across nodes
+    w.S0 = np.zeros_like(w.S0)
+    w.alpha = np.ones_like(w.alpha)
+    w.beta = np.full_like(w.beta, 0.5)
+    w.q, w.k, w.v = np.zeros_like(w.q), np.zeros_like(w.k), np.zeros_like(w.v)
+    w.q[0, :, 0, 0:4] = hot
+    w.k[0, :, 0, 20] = hot
+    w.k[0, 100, 0], w.k[0, 50, 0] = 0.0, 0.0
+    w.k[0, 100, 0, 3:7] = hot
+    w.k[0, 50, 0, 5] = hot
+    w.beta[0, 100, 0] = beta
+    w.v[0, 50, 0, 2] = 1024.0
+    print(f"[gpu] beta = {beta:g}", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    ref, got = orc.verify(w)[0, 100:, 0, 2], dt.out.cpu().numpy()[0, 100:, 0, 2]
+    assert (ref < 0).all()
+    err = np.max(np.abs(got / ref - 1))
+    print(f"[gpu]   err {err:.3e}", flush=True)
+    # c = beta / 4 and x = c / 2 are split once or twice, off by at most 2^-38 each
+    assert err <= 2.0 ** -20 + 3 * 2.0 ** -38 / (beta / 8)
+
+
+@pytest.mark.parametrize("beta", [-0.5, 2.0, 3.0])
+def test_writes_that_grow_the_query(G, orc, beta):
+    """beta outside (0, 1], up to where q~ grows along the path."""
+    import torch
+    T = 180
+    w = W.make_random(9660, 2, T, 1, 2, 16, 32, "f32", shuffle=True)
+    w.beta[:, ::3] = beta
+    print(f"[gpu] beta = {beta}", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    ref = orc.verify(w)
+    err = np.max(np.abs(dt.out.cpu().numpy() - ref)) / np.max(np.abs(ref))
+    print(f"[gpu]   err {err:.3e}", flush=True)
+    assert err <= 2 * O_TOL  # an error is amplified as q~ is
