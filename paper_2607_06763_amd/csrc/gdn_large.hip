@@ -424,31 +424,27 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
       float f = qk ? rsqrt_hw(ss + 1e-6f) : 1.0f;
       const bool st = ok && g0 + u < np;
       if constexpr (kHalf) {
-        // v~: one power-of-two scale per (position, head) from the row's
-        // largest finite value (an inf must not flush the rest of its row)
+        // v~: one power-of-two scale per (position, head) from the row max
         float mx = 0.0f;
 #pragma unroll
         for (int j = 0; j < CPT; ++j) mx = fmaxf(mx, fabsf(y[j]));
-        float bad = 0.0f;
-        if (odd) {  // wave-uniform, rare
-          mx = 0.0f;
+        float sc, inv;
+        row_scale(group_absmax<VG>(mx), sc, inv);
+        if (odd) {  // wave-uniform, rare (one branch: two cost 1 us of latency in small launches)
+          float fin = 0.0f, t = 0.0f;
 #pragma unroll
           for (int j = 0; j < CPT; ++j) {
-            const float a = fabsf(y[j]);
-            if (a < __builtin_inff())
-              mx = fmaxf(mx, a);
+            if (fabsf(y[j]) < __builtin_inff())
+              fin = fmaxf(fin, fabsf(y[j]));
             else
-              bad = 1.0f;  // holds inf or NaN
+              t = 1.0f;  // holds inf or NaN
           }
-        }
-        mx = group_absmax<VG>(mx);
-        float sc, inv;
-        row_scale(mx, sc, inv);
-        if (odd) {
+          // the row's largest finite value: an inf must not flush the rest
+          row_scale(group_absmax<VG>(fin), sc, inv);
           // a q or k row with one is NaN throughout; a v row says so by the
           // sign of its scale
-          if (qk && group_max<DK / CPT>(bad) != 0.0f) f = __builtin_nanf("");
-          if (!qk && group_max<(kHalf ? VG : 1)>(bad) != 0.0f) inv = -inv;
+          if (qk && group_max<DK / CPT>(t) != 0.0f) f = __builtin_nanf("");
+          if (!qk && group_max<(kHalf ? VG : 1)>(t) != 0.0f) inv = -inv;
         }
         const float g = qk ? f : sc;
         uint2 h4[CPT / 4];
