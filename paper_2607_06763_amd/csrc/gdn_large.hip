@@ -183,24 +183,42 @@ __device__ __forceinline__ void depth_first_order(const MetaPtrs& m, size_t bt, 
   int* s_at = s + 4 * kLMaxT;  // index by position
   constexpr int NP = kLMaxT / kFT;  // positions per thread
   const int tid = threadIdx.x;
-  int dep[NP];
+  // the last position is the deepest (depth order)
+  const int last = m.pdep[bt + nval - 1], deepest = last < T ? last : T - 1;
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
     const int i = u * kFT + tid;
-    dep[u] = i < nval ? m.pdep[bt + i] : -1;
     const int pp = i < nval ? m.ppos[bt + i] : -1;
     // a parent comes first (depth order); anything else is corrupt metadata
     s_pp[i] = pp >= 0 && pp < i ? pp : -1;
+    s_nx[i] = s_pp[i];
     s_size[i] = 1;
   }
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < NP; ++u) {
-    const int i = u * kFT + tid;
-    for (int a = i < nval ? s_pp[i] : -1; a >= 0; a = s_pp[a]) atomicAdd(&s_size[a], 1);
-  }
-  __syncthreads();
+  // subtree sizes by doubling: round r adds to every node the sizes, down to
+  // distance 2^r, of the nodes 2^r below it.  With one addition per (node,
+  // ancestor) the launch took 51 instead of 34 us on 8 chains of 512.
   int size[NP], sum[NP];
+  for (int span = 1; span <= deepest; span <<= 1) {
+    int nx[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      size[u] = s_size[u * kFT + tid];
+      nx[u] = s_nx[u * kFT + tid];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      if (nx[u] >= 0) {
+        atomicAdd(&s_size[nx[u]], size[u]);
+        nx[u] = s_nx[nx[u]];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NP; ++u) s_nx[u * kFT + tid] = nx[u];
+    __syncthreads();
+  }
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
     const int i = u * kFT + tid;
@@ -231,7 +249,7 @@ __device__ __forceinline__ void depth_first_order(const MetaPtrs& m, size_t bt, 
     s_nx[u * kFT + tid] = s_pp[u * kFT + tid];
   }
   __syncthreads();
-  for (int span = 1; span < T; span <<= 1) {
+  for (int span = 1; span <= deepest; span <<= 1) {
     int nx[NP];
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
