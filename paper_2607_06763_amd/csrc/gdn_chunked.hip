@@ -16,7 +16,7 @@
 // (I - N)(I + N^2)(I + N^4)(I + N^8), N the tile of X_jj (N^16 = 0), formed by
 // repeated squaring, and the tile below them is -V11 X10 V00 (V the inverses).
 //
-// Three launches:
+// Three launches (two up to 32 slots, see chunk_kernel):
 //   features           (gdn_large.hip) fp32 rows F[B][T][C]
 //   chunk_gram_kernel  one workgroup per (position block j, up to 4 blocks c <=
 //                      j, key head, sequence): the Gram blocks K_j K_c^T and
@@ -165,13 +165,93 @@ __device__ __forceinline__ void inverse16(f32x4 a, f32x4 at, f32x4& v, f32x4& vt
   }
 }
 
+// One wave: the decayed, masked Y_jj and the inverse of I + X_jj of a value
+// head, 32 rows of stride RS each, from the Gram blocks K_j K_j^T, Q_j K_j^T in
+// s_g.  ga, gb, gp: alpha, beta and the parent's row (below 0 outside the
+// block) of row lane % 32; rows: rows with nodes; s_a: kDiagLds floats.
+constexpr int kDiagLds = kBc * kLs + 3 * kBc;
+template <int RS>
+__device__ __forceinline__ void diag_block(const float* s_g, float* s_a, float ga, float gb, int gp, int rows, int lane,
+                                           float* dst) {
+  const int l16 = lane & 15, m = lane >> 4;
+  const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+  float* s_la = s_a + kBc * kLs;
+  float* s_be = s_la + kBc;
+  uint32_t* s_up = reinterpret_cast<uint32_t*>(s_be + kBc);  // strict ancestors in the block, one bit each
+  {  // log decay from the block's edge down to each row, and its ancestors in
+     // the block, by pointer jumping over the lanes
+    const int i = lane & (kBc - 1);
+    const bool real = i < rows;
+    // floored at the smallest normal float: a decay of 0 keeps ratios finite
+    float sl = real ? fmaxf(log2f(ga), kMinLog2) : 0.0f;
+    const float be = real ? gb : 0.0f;
+    int nx = real ? gp : -1;
+    uint32_t up = nx >= 0 ? 1u << nx : 0u;
+#pragma unroll
+    for (int s = 0; s < 5; ++s) {
+      const int src = nx >= 0 ? nx : i;
+      const float sl2 = __shfl(sl, src);
+      const uint32_t up2 = __shfl(up, src);
+      const int nx2 = __shfl(nx, src);
+      if (nx >= 0) {
+        sl += sl2;
+        up |= up2;
+        nx = nx2;
+      }
+    }
+    s_la[i] = sl;
+    s_be[i] = be;
+    s_up[i] = up;
+  }
+  wave_lds_order();
+  {  // A = -X_jj -> LDS, Y_jj -> workspace: 16 columns of one row per lane
+    const int i = lane & (kBc - 1), cc = 16 * (lane >> 5);
+    const float la = s_la[i], be = s_be[i];
+    const uint32_t up = s_up[i];
+    const bool real = i < rows;
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) {
+      const float4 x = *reinterpret_cast<const float4*>(s_g + i * kLs + cc + q);
+      const float4 y = *reinterpret_cast<const float4*>(s_g + kBc * kLs + i * kLs + cc + q);
+      const f32x4 gx = as_x4(x), gy = as_x4(y);
+      f32x4 av, yv;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = cc + q + e;
+        const bool anc = (up >> c) & 1;
+        const float r = __builtin_amdgcn_exp2f(la - s_la[c]);
+        av[e] = anc ? -be * r * gx[e] : 0.0f;
+        yv[e] = anc || (c == i && real) ? r * gy[e] : 0.0f;
+      }
+      *reinterpret_cast<float4*>(s_a + i * kLs + cc + q) = make_float4(av[0], av[1], av[2], av[3]);
+      *reinterpret_cast<float4*>(dst + kBc * RS + i * RS + cc + q) = make_float4(yv[0], yv[1], yv[2], yv[3]);
+    }
+  }
+  wave_lds_order();
+  // (I + X_jj)^-1 from its 16 x 16 tiles: V00, V11 and V11 A10 V00
+  f32x4 v[2], vt[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    f32x4 a;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = s_a[(16 * t + 4 * m + e) * kLs + 16 * t + l16];
+    const f32x4 at = as_x4(*reinterpret_cast<const float4*>(s_a + (16 * t + l16) * kLs + 16 * t + 4 * m));
+    inverse16(a, at, v[t], vt[t], l16, m);
+  }
+  const f32x4 at10 = as_x4(*reinterpret_cast<const float4*>(s_a + (16 + l16) * kLs + 4 * m));
+  const f32x4 vt10 = mm_f(mm_f(at10, v[0], z4), vt[1], z4);
+  *reinterpret_cast<float4*>(dst + l16 * RS + 4 * m) = make_float4(vt[0][0], vt[0][1], vt[0][2], vt[0][3]);
+  *reinterpret_cast<float4*>(dst + (16 + l16) * RS + 4 * m) = make_float4(vt10[0], vt10[1], vt10[2], vt10[3]);
+  *reinterpret_cast<float4*>(dst + (16 + l16) * RS + 16 + 4 * m) = make_float4(vt[1][0], vt[1][1], vt[1][2], vt[1][3]);
+}
+
 template <int DK>
 struct GramSmem {
   static constexpr int KP = DK < 32 ? 32 : DK;  // contraction extent of the key products (zero padded)
   static constexpr int LKH = KP + 8;            // bf16 plane row (halves)
   static constexpr size_t planes = size_t(6) * kBc * LKH * 2;  // q_j, k_j, k_c (hi, lo)
   static constexpr size_t mat = size_t(kBc) * kLs * 4;
-  static constexpr size_t diag = 2 * mat + (kHT / 64) * (mat + 3 * kBc * 4);  // Gram, then per wave A and its rows' gates
+  static constexpr size_t diag = 2 * mat + (kHT / 64) * kDiagLds * 4;  // Gram, then per wave A and its rows' gates
   static constexpr size_t uni = planes > diag ? planes : diag;
   static constexpr size_t total = uni + size_t(kBc) * kHW * 8;  // ancestor words of block j
   static_assert(total <= 53 * 1024, "three workgroups per CU");
@@ -324,82 +404,15 @@ __global__ __launch_bounds__(kHT, 6) void chunk_gram_kernel(ChunkParams p) {
                               s_kh + 16 * tc * LKH, s_kl + 16 * tc * LKH, LKH, z4, lane);
   __syncthreads();  // the planes are read: LDS holds the Gram blocks from here
   float* s_g = reinterpret_cast<float*>(smem);  // [2][32][kLs]
-  float* s_a = s_g + 2 * kBc * kLs + wave * (kBc * kLs + 3 * kBc);
-  float* s_la = s_a + kBc * kLs;
-  float* s_be = s_la + kBc;
-  uint32_t* s_up = reinterpret_cast<uint32_t*>(s_be + kBc);  // strict ancestors in the block, one bit each
+  float* s_a = s_g + 2 * kBc * kLs + wave * kDiagLds;
 #pragma unroll
   for (int e = 0; e < 4; ++e) s_g[kind * kBc * kLs + (16 * ti + 4 * m + e) * kLs + 16 * tc + l16] = gm[e];
   __syncthreads();
   for (int w = wave; w < G; w += kHT / 64) {
     const int h = g * G + w;
-    {  // log decay from the block's edge down to each row, and its ancestors in
-       // the block, by pointer jumping over the lanes
-      const int i = lane & (kBc - 1), pos = kBc * jb + i;
-      const bool real = pos < nval;
-      if (w != wave) fetch_gates(h);
-      // floored at the smallest normal float: a decay of 0 keeps ratios finite
-      float sl = real ? fmaxf(log2f(ga), kMinLog2) : 0.0f;
-      const float be = real ? gb : 0.0f;
-      int nx = real ? gp - kBc * jb : -1;
-      uint32_t up = nx >= 0 ? 1u << nx : 0u;
-#pragma unroll
-      for (int s = 0; s < 5; ++s) {
-        const int src = nx >= 0 ? nx : i;
-        const float sl2 = __shfl(sl, src);
-        const uint32_t up2 = __shfl(up, src);
-        const int nx2 = __shfl(nx, src);
-        if (nx >= 0) {
-          sl += sl2;
-          up |= up2;
-          nx = nx2;
-        }
-      }
-      s_la[i] = sl;
-      s_be[i] = be;
-      s_up[i] = up;
-    }
-    wave_lds_order();
-    float* dst = p.D + ((size_t(b) * Hv + h) * NB + jb) * (2 * kBc * kBc);
-    {  // A = -X_jj -> LDS, Y_jj -> workspace: 16 columns of one row per lane
-      const int i = lane & (kBc - 1), cc = 16 * (lane >> 5);
-      const float la = s_la[i], be = s_be[i];
-      const uint32_t up = s_up[i];
-      const bool real = kBc * jb + i < nval;
-#pragma unroll
-      for (int q = 0; q < 16; q += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(s_g + i * kLs + cc + q);
-        const float4 y = *reinterpret_cast<const float4*>(s_g + kBc * kLs + i * kLs + cc + q);
-        const f32x4 gx = as_x4(x), gy = as_x4(y);
-        f32x4 av, yv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int c = cc + q + e;
-          const bool anc = (up >> c) & 1;
-          const float r = __builtin_amdgcn_exp2f(la - s_la[c]);
-          av[e] = anc ? -be * r * gx[e] : 0.0f;
-          yv[e] = anc || (c == i && real) ? r * gy[e] : 0.0f;
-        }
-        *reinterpret_cast<float4*>(s_a + i * kLs + cc + q) = make_float4(av[0], av[1], av[2], av[3]);
-        *reinterpret_cast<float4*>(dst + kBc * kBc + i * kBc + cc + q) = make_float4(yv[0], yv[1], yv[2], yv[3]);
-      }
-    }
-    wave_lds_order();
-    // (I + X_jj)^-1 from its 16 x 16 tiles: V00, V11 and V11 A10 V00
-    f32x4 v[2], vt[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      f32x4 a;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = s_a[(16 * t + 4 * m + e) * kLs + 16 * t + l16];
-      const f32x4 at = as_x4(*reinterpret_cast<const float4*>(s_a + (16 * t + l16) * kLs + 16 * t + 4 * m));
-      inverse16(a, at, v[t], vt[t], l16, m);
-    }
-    const f32x4 at10 = as_x4(*reinterpret_cast<const float4*>(s_a + (16 + l16) * kLs + 4 * m));
-    const f32x4 vt10 = mm_f(mm_f(at10, v[0], z4), vt[1], z4);
-    *reinterpret_cast<float4*>(dst + l16 * kBc + 4 * m) = make_float4(vt[0][0], vt[0][1], vt[0][2], vt[0][3]);
-    *reinterpret_cast<float4*>(dst + (16 + l16) * kBc + 4 * m) = make_float4(vt10[0], vt10[1], vt10[2], vt10[3]);
-    *reinterpret_cast<float4*>(dst + (16 + l16) * kBc + 16 + 4 * m) = make_float4(vt[1][0], vt[1][1], vt[1][2], vt[1][3]);
+    if (w != wave) fetch_gates(h);
+    diag_block<kBc>(s_g, s_a, ga, gb, gp - kBc * jb, nval - kBc * jb, lane,
+                    p.D + ((size_t(b) * Hv + h) * NB + jb) * (2 * kBc * kBc));
     wave_lds_order();
   }
 }
@@ -415,7 +428,12 @@ struct ChunkSmem {
   static constexpr size_t total = qk + xy + diag + meta;
 };
 
-template <int DK, int DV, typename TIn>
+// ONE: trees of at most 32 slots, i.e. one block.  The workgroup then forms its
+// head's Gram block and diagonal matrices itself: the launch of their own took 5
+// to 12 us, the work in here 2 to 8.  Whole calls: 1 x 9 slots of a toy layer
+// 16.6 -> 13.6 us, 8 x 12 slots, 16 / 32 heads of 64: 19.6 -> 16.3, 8 x 32 and
+// 32 x 32, 16 / 48 heads of 128: 40.4 -> 36.4 and 72.7 -> 68.1.
+template <int DK, int DV, typename TIn, bool ONE>
 __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
   using SM = ChunkSmem<DK, DV>;
   constexpr int KP = SM::KP, LKH = SM::LKH;
@@ -525,8 +543,10 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
   float4 dg;
   auto fetch_top = [&](int jb) {
     const int tid = opaque(threadIdx.x), lane = tid & 63, l16 = lane & 15, m = lane >> 4;
-    flag = p.need[(size_t(b) * NB + jb) * kMaxNB + (lane < jb ? lane : 0)];
-    dg = *reinterpret_cast<const float4*>(Db + size_t(jb) * (2 * kBc * kBc) + 4 * tid);
+    if constexpr (!ONE) {
+      flag = p.need[(size_t(b) * NB + jb) * kMaxNB + (lane < jb ? lane : 0)];
+      dg = *reinterpret_cast<const float4*>(Db + size_t(jb) * (2 * kBc * kBc) + 4 * tid);
+    }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -539,6 +559,17 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
   static_assert(kHT * 4 == 2 * kBc * kBc, "a float4 of the diagonal matrices per thread");
   fetch_qk(0);
   fetch_top(0);
+  constexpr int kDiagWave = kHT / 64 - 1;  // ONE: the last to have channels
+  float ga = 0.0f, gb = 0.0f;
+  int gp = -1;
+  if constexpr (ONE) {
+    if (wave == kDiagWave) {
+      const int pc = (lane & (kBc - 1)) < nval ? lane & (kBc - 1) : 0, nd = m_.order[bt + pc];
+      ga = ld(alpha, (bt + nd) * Hv + h);
+      gb = ld(beta, (bt + nd) * Hv + h);
+      gp = m_.ppos[bt + pc];
+    }
+  }
   // ---- this wave's rows of S0 as operands: channel 16 wave + l16, columns
   //      32 ks + 8 m .. + 7
   bf16x8 sh[NKS], sl_[NKS];
@@ -589,7 +620,7 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
     const int tid = opaque(threadIdx.x), lane = tid & 63, l16 = lane & 15, m = lane >> 4;
     const int col = 16 * wave + l16;
     const int xi = tid / (kBc / 2), xc = 2 * (tid % (kBc / 2));  // this thread's X, Y elements: row, columns xc, xc + 1
-    uint32_t need = uint32_t(__ballot(lane < jb && flag != 0));
+    uint32_t need = ONE ? 0u : uint32_t(__ballot(lane < jb && flag != 0));
     // Gram blocks of a group, two elements of each per thread
     float2 gx[kCP], gy[kCP];
     uint32_t gm[kCP];
@@ -598,6 +629,7 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
 #pragma unroll
       for (int q = 0; q < kCP; ++q) {
         cs[q] = need ? __ffs(int(need)) - 1 : -1;
+        if constexpr (ONE) continue;
         need &= need - 1u;
         const int c = cs[q] >= 0 ? cs[q] : 0;  // loads without a branch, unused where there is no block
         const float* gp = Gb + (size_t(jb) * (jb - 1) / 2 + c) * (2 * kBc * kBc) + xi * kBc + xc;
@@ -609,8 +641,19 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
     fetch_group();
     __syncthreads();  // LDS of the block before is read (first block: s_la is written)
     store_qk(jb);
-    *reinterpret_cast<float4*>(s_d + tid / 8 * kLs + 4 * (tid % 8)) = dg;  // tile (0, 1) of neither is read
+    if constexpr (!ONE) *reinterpret_cast<float4*>(s_d + tid / 8 * kLs + 4 * (tid % 8)) = dg;  // tile (0, 1) of neither is read
     __syncthreads();
+    if constexpr (ONE) {
+      float* s_g = reinterpret_cast<float*>(s_xy);  // the Gram blocks, then a wave's diagonal matrices
+      static_assert((2 * kBc * kLs + kDiagLds) * 4 <= SM::xy, "Gram blocks in the place of X and Y");
+      const int kind = wave >> 2, ti = (wave >> 1) & 1, tc = wave & 1;
+      const f32x4 gm = mm16x3<KP>((kind ? s_qh : s_kh) + 16 * ti * LKH, (kind ? s_ql : s_kl) + 16 * ti * LKH, LKH,
+                                  s_kh + 16 * tc * LKH, s_kl + 16 * tc * LKH, LKH, f32x4{0.f, 0.f, 0.f, 0.f}, lane);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s_g[kind * kBc * kLs + (16 * ti + 4 * m + e) * kLs + 16 * tc + l16] = gm[e];
+      __syncthreads();
+      if (wave == kDiagWave) diag_block<kLs>(s_g, s_g + 2 * kBc * kLs, ga, gb, gp, nval, lane, s_d);
+    }
     // ---- O_j = a Q S0^T, R_j = beta (V - a K S0^T)
     f32x4 rr[2] = {z4, z4}, oo[2] = {z4, z4};
     if (chan) {
@@ -689,6 +732,7 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
       fetch_qk(jb + 1);
       fetch_top(jb + 1);
     }
+    if constexpr (ONE) __syncthreads();  // the diagonal matrices are written
     // ---- U_j = (I + X_jj)^-1 R_j, kept as operands of the later blocks
     if (chan) {
       const float* vp = s_d + l16 * kLs + 4 * m;
@@ -697,7 +741,7 @@ __global__ __launch_bounds__(kHT, 4) void chunk_kernel(ChunkParams p) {
       const f32x4 v00 = tile(vp), v10 = tile(vp + 16 * kLs), v11 = tile(vp + 16 * kLs + 16);
       const f32x4 y00 = tile(yp), y10 = tile(yp + 16 * kLs), y11 = tile(yp + 16 * kLs + 16);
       const f32x4 u0 = mm_f(v00, rr[0], z4), u1 = mm_f(v11, rr[1], mm_f(v10, rr[0], z4));
-      {
+      if constexpr (!ONE) {
         const float x[8] = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
         bf16x8 hi, lo;
         split8(x, hi, lo);
@@ -733,20 +777,22 @@ template <int DK, int DV, typename TIn>
 static int launch_chunk_t(const ChunkParams& p, hipStream_t stream) {
   using SM = ChunkSmem<DK, DV>;
   using SG = GramSmem<DK>;
-  int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_kernel<DK, DV, TIn>), int(SM::total),
-                              "verify_chunked");
-  if (rc != GDN_OK) return rc;
-  rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_gram_kernel<DK, TIn>), int(SG::total),
-                          "verify_chunked");
-  if (rc != GDN_OK) return rc;
   const int NB = (p.T + kBc - 1) / kBc, G = p.Hv / p.Hk, units = p.B * p.Hk;
-  int groups = 0;
-  for (int j = 0; j < NB; ++j) groups += j / kCG + 1;
-  hipLaunchKernelGGL((chunk_gram_kernel<DK, TIn>), dim3(p.Hk, groups, p.B), dim3(kHT), SG::total, stream, p);
+  const auto cascade = NB == 1 ? &chunk_kernel<DK, DV, TIn, true> : &chunk_kernel<DK, DV, TIn, false>;
+  int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(cascade), int(SM::total), "verify_chunked");
+  if (rc != GDN_OK) return rc;
+  if (NB > 1) {
+    rc = ensure_dynamic_lds(reinterpret_cast<const void*>(&chunk_gram_kernel<DK, TIn>), int(SG::total),
+                            "verify_chunked");
+    if (rc != GDN_OK) return rc;
+    int groups = 0;
+    for (int j = 0; j < NB; ++j) groups += j / kCG + 1;
+    hipLaunchKernelGGL((chunk_gram_kernel<DK, TIn>), dim3(p.Hk, groups, p.B), dim3(kHT), SG::total, stream, p);
+  }
   // whole groups of 8 G blocks; rows of the grid keep its width below the limit
   const int rows = (units + 7) / 8, wide = (1 << 19) / G > 0 ? (1 << 19) / G : 1;
   const dim3 grid(unsigned(rows < wide ? rows : wide) * 8u * G, (rows + wide - 1) / wide);
-  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), grid, dim3(kHT), SM::total, stream, p);
+  hipLaunchKernelGGL(cascade, grid, dim3(kHT), SM::total, stream, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(GDN_EHIP, "verify_chunked launch: %s", hipGetErrorString(e));
   return GDN_OK;

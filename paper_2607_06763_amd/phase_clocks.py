@@ -117,7 +117,7 @@ def _instrument_chunked(src: str) -> str:
         "      TS(7 + 4 * jb);\n      // ---- O_j += Y_jj U_j, scaled and stored\n")
     rep("      }\n    }\n  }\n}\n\n// ---------------------------------------------------------------------------\n// Launch: features",
         "      }\n    }\n  }\n  TS(127);\n}\n\n// ---------------------------------------------------------------------------\n// Launch: features")
-    launch = "  hipLaunchKernelGGL((chunk_kernel<DK, DV, TIn>), grid, dim3(kHT), SM::total, stream, p);"
+    launch = "  hipLaunchKernelGGL(cascade, grid, dim3(kHT), SM::total, stream, p);"
     rep(launch,
         "  const_cast<ChunkParams&>(p).stamps = g_stamps;\n  const_cast<ChunkParams&>(p).stamp_cap = g_stamp_cap;\n" + launch)
     src += ('\nextern "C" void gdn_chunk_stamps(void* buf, long long cap_blocks) {\n'
