@@ -133,8 +133,8 @@ int gdn_tree_prepare(const gdn_dims* dims, const int32_t* parent, void* meta,
  * Up to 128 slots everything stays on chip and nothing is allocated; above
  * 128 the post-conv features go through a device workspace of
  * B T (2 C + 4 Hv) bytes (fp16 features, fp32 scales of the value rows;
- * C = 2 Hk dk + Hv dv, the first part rounded up to 256 bytes) and 3 KB per
- * tree (its depth-first order) that the
+ * C = 2 Hk dk + Hv dv, the first part rounded up to 256 bytes) and 6 T bytes
+ * per tree (its depth-first order, T rounded up to 16) that the
  * library allocates on the first call that needs it and keeps per
  * (device, stream) until the process ends (a call under stream capture that
  * would have to grow it returns GDN_EUNSUPPORTED).
@@ -158,8 +158,9 @@ int gdn_tree_verify(const gdn_dims* dims, const void* meta, const void* q, const
  * it runs; it calls no allocating routine.  Trees of more than 128 slots
  * need the feature workspace of gdn_tree_verify, B T (2 C + 4 Hv) bytes:
  * here it is a static device array of GDN_NOALLOC_SCRATCH_BYTES that the
- * library holds on every device it runs on until the process ends (with 16
- * MB for the orders of the trees), and larger problems return GDN_EUNSUPPORTED before any device work.  All
+ * library holds on every device it runs on until the process ends (with 4.5
+ * MB for the orders of the trees), and larger problems return
+ * GDN_EUNSUPPORTED before any device work.  All
  * calls on one device share that array: calls that overlap in time on one
  * device (different streams, or host threads) race and must be serialized
  * by the caller. */

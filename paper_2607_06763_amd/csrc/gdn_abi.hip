@@ -58,11 +58,11 @@ static int check_dims(const gdn_dims* d, const char* who) {
 }
 
 // Verification at any supported T: the LDS-resident kernel up to 128 slots,
-// the feature workspace + gathered pull-back above.
+// the feature workspace + tiled pull-back above.
 static int verify_any(const VerifyArgs& a, hipStream_t stream) {
   if (a.T <= kSmallMaxT) return launch_verify(a, stream);
   const size_t bytes =
-      large_order_offset(large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv)) + large_order_bytes(a.B);
+      large_order_offset(large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv)) + large_order_bytes(a.B, a.T);
   int rc = GDN_OK;
   void* ws = stream_workspace(bytes, stream, &rc);
   if (!ws) return rc;

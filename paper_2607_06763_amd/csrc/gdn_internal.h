@@ -359,7 +359,8 @@ size_t large_workspace_bytes(int B, int T, int Hk, int Hv, int dk, int dv);
 // The depth-first order of the trees (three 16-bit arrays each) follows the
 // features at the next multiple of 256 bytes.
 inline size_t large_order_offset(size_t workspace_bytes) { return (workspace_bytes + 255) & ~size_t(255); }
-inline size_t large_order_bytes(int B) { return size_t(B) * 3 * GDN_MAX_T * sizeof(int16_t); }
+__host__ __device__ constexpr int large_order_stride(int T) { return (T + 15) & ~15; }
+inline size_t large_order_bytes(int B, int T) { return size_t(B) * 3 * large_order_stride(T) * sizeof(int16_t); }
 // ws: the features and the order
 int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 // A device buffer of at least bytes for work on stream, cached per (device,

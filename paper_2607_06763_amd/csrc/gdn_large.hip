@@ -72,8 +72,9 @@ struct LargeParams {
   float* F;       // fp32 features [B][T][C] (chunked form)
   _Float16* FH;   // fp16 features [B][T][C] (pull-back)
   float* Vs;      // inverse v~ row scales [B][T][Hv] (pull-back), negative: the row holds values that are not finite
-  // depth-first order [B][3][kLMaxT] (pull-back): canonical position and end
-  // of the subtree by depth-first index; path of each 16-node tile
+  // depth-first order [B][3][large_order_stride(T)] (pull-back): canonical
+  // position and end of the subtree by depth-first index; path of each 16-node
+  // tile
   int16_t* ord;
   // fused step: the previous step's commit, run by the pull-back on the rows
   // it reads (conv_state above is then the conv state after the commit)
@@ -168,8 +169,8 @@ __device__ __forceinline__ float group_absmax(float v) {
 }
 
 // Depth-first order of tree b, children by canonical position: ord[i] is the
-// canonical position of the i-th node, ord[kLMaxT + i] the end of its subtree,
-// ord[2 kLMaxT + 16 j + tau] the indices of the nearest 16 proper ancestors of
+// canonical position of the i-th node, ord[st + i] the end of its subtree,
+// ord[2 st + 16 j + tau] (st: large_order_stride(T)) the indices of the nearest 16 proper ancestors of
 // node 16 j, nearest last (kLMaxT: none).  One workgroup of kFT threads; s: 5
 // kLMaxT ints.  A node's index is the sum over
 // its path, without the root, of 1 + the subtree sizes of the siblings before
@@ -182,7 +183,7 @@ __device__ __forceinline__ void depth_first_order(const MetaPtrs& m, size_t bt, 
   int* s_nx = s + 3 * kLMaxT;  // pointer jumping: 2^r-th ancestor; then the parent's index by index
   int* s_at = s + 4 * kLMaxT;  // index by position
   constexpr int NP = kLMaxT / kFT;  // positions per thread
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, st = large_order_stride(T);
   // the last position is the deepest (depth order)
   const int last = m.pdep[bt + nval - 1], deepest = last < T ? last : T - 1;
 #pragma unroll
@@ -274,7 +275,7 @@ __device__ __forceinline__ void depth_first_order(const MetaPtrs& m, size_t bt, 
       const int at = sum[u] < nval ? sum[u] : nval - 1;  // a permutation of 0 .. nval - 1
       s_at[i] = at;
       ord[at] = int16_t(i);
-      ord[kLMaxT + at] = int16_t(at + size[u] < nval ? at + size[u] : nval);
+      ord[st + at] = int16_t(at + size[u] < nval ? at + size[u] : nval);
     }
   }
   __syncthreads();
@@ -288,7 +289,7 @@ __device__ __forceinline__ void depth_first_order(const MetaPtrs& m, size_t bt, 
     int a = s_nx[kLTile * tid];
     for (int tau = kLTile - 1; tau >= 0; --tau) {
       a = a < kLTile * tid ? a : -1;  // ancestors come first
-      ord[2 * kLMaxT + kLTile * tid + tau] = int16_t(a >= 0 ? a : kLMaxT);
+      ord[2 * st + kLTile * tid + tau] = int16_t(a >= 0 ? a : kLMaxT);
       a = a >= 0 ? s_nx[a] : -1;
     }
   }
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
       const MetaPtrs m = meta_ptrs(p.meta, p.B, p.T);
       const int nval = m.status[b] == GDN_TREE_OK ? m.nvalid[b] : 0;
       if (nval > 0)
-        depth_first_order(m, size_t(b) * p.T, p.T, nval < p.T ? nval : p.T, p.ord + size_t(b) * 3 * kLMaxT,
+        depth_first_order(m, size_t(b) * p.T, p.T, nval < p.T ? nval : p.T, p.ord + size_t(b) * 3 * large_order_stride(p.T),
                           reinterpret_cast<int*>(s_cs));
       return;
     }
@@ -652,14 +653,15 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     }
   }
   // ---- order and this head's gates by depth-first index
-  const int16_t* ord = p.ord + size_t(b) * 3 * kLMaxT;
+  const int ost = large_order_stride(T);
+  const int16_t* ord = p.ord + size_t(b) * 3 * ost;
   bool grows = false;
   for (int j = tid; j <= kLMaxT; j += kLT) {
     const bool real = j < nval;
     int row = nval > 0 ? ord[real ? j : nval - 1] : 0;  // past the nodes: the last one's row
-    const int end = ord[kLMaxT + (real ? j : 0)];
+    const int end = ord[ost + (real ? j : 0)];
     const bool live = j / kLTile * kLTile < nval;  // a tile with nodes
-    const int a = ord[2 * kLMaxT + (live ? j : 0)];
+    const int a = ord[2 * ost + (live ? j : 0)];
     row = row >= 0 && row < T ? row : 0;
     RowGate g = {0.0f, 0.0f, 0.0f, 0};
     // the scale, and with it the mark, of the row that is loaded: an absent
@@ -1127,7 +1129,7 @@ static int launch_large(const VerifyArgs& a, void* ws, void* ord, hipStream_t st
 int launch_verify_large(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (a.T > kLMaxT) return set_error(GDN_EUNSUPPORTED, "verify: T=%d exceeds %d", a.T, kLMaxT);
   const size_t order = large_order_offset(large_workspace_bytes(a.B, a.T, a.Hk, a.Hv, a.dk, a.dv));
-  if (ws_bytes < order + large_order_bytes(a.B))
+  if (ws_bytes < order + large_order_bytes(a.B, a.T))
     return set_error(GDN_EINVAL, "verify: workspace of %zu bytes is too small", ws_bytes);
   return launch_large(a, ws, static_cast<unsigned char*>(ws) + order, stream);
 }
@@ -1167,10 +1169,11 @@ int launch_features(const VerifyArgs& a, float* F, hipStream_t stream) {
 // written before they are read, so nothing needs clearing.
 // ---------------------------------------------------------------------------
 static __device__ __align__(256) unsigned char scratch[GDN_NOALLOC_SCRATCH_BYTES];
-// the depth-first orders of the same problems: at least 129 nodes per tree of
-// at least 100 bytes (one key and one value head of 16)
-static __device__ __align__(256) unsigned char
-    order_scratch[size_t(GDN_NOALLOC_SCRATCH_BYTES) / ((kSmallMaxT + 1) * 100) * 3 * kLMaxT * sizeof(int16_t)];
+// The depth-first orders of the same problems: a node takes at least 100 bytes
+// above (one key and one value head of 16), and in here 6, with its tree's
+// nodes rounded up to a multiple of 16: most for 129.
+constexpr size_t kOrderTrees = size_t(GDN_NOALLOC_SCRATCH_BYTES) / (100 * (kSmallMaxT + 1)) + 1;
+static __device__ __align__(256) unsigned char order_scratch[kOrderTrees * 6 * large_order_stride(kSmallMaxT + 1)];
 
 static void* scratch_address(const void* symbol, int* rc) {
   static std::mutex mu;
@@ -1202,6 +1205,9 @@ int launch_verify_noalloc(const VerifyArgs& a, hipStream_t stream) {
                      "verify_noalloc: B=%d T=%d needs %zu workspace bytes, above the static %zu (call "
                      "gdn_tree_verify, or split the batch)",
                      a.B, a.T, bytes, size_t(GDN_NOALLOC_SCRATCH_BYTES));
+  if (large_order_bytes(a.B, a.T) > sizeof(order_scratch))
+    return set_error(GDN_EUNSUPPORTED, "verify_noalloc: B=%d T=%d: orders above the static %zu bytes", a.B, a.T,
+                     sizeof(order_scratch));
   int rc = GDN_OK;
   void* ws = scratch_address(HIP_SYMBOL(scratch), &rc);
   if (!ws) return rc;

@@ -65,3 +65,30 @@ def test_noalloc_refuses_oversize(G):
     fake = [ctypes.c_void_p(0x1000)] * 10       # never dereferenced: refused on the host
     assert L.gdn_tree_verify_noalloc(ctypes.byref(d), *fake, None) == G.GDN_EUNSUPPORTED
     assert "workspace" in G.last_error()
+
+
+@pytest.mark.parametrize("T", [129, 144, 145, 512])
+def test_noalloc_largest_batch(G, T):
+    """As many trees as the static array takes (one key and one value head of
+    16: the most trees), whose orders have an array of their own."""
+    import torch
+    B = G.NOALLOC_SCRATCH_BYTES // (T * 100)
+    while -(-B * T * 96 // 256) * 256 + B * T * 4 > G.NOALLOC_SCRATCH_BYTES:
+        B -= 1
+    print(f"[gpu] noalloc B={B} T={T}", flush=True)
+    one = W.make_random(8150 + T, 8, T, 1, 1, 16, 16, "bf16", shuffle=True)
+    for name in ("parent", "q", "k", "v", "alpha", "beta", "S0", "conv_state", "accepted"):
+        x = getattr(one, name)
+        setattr(one, name, np.ascontiguousarray(np.resize(x, (B,) + x.shape[1:])))
+    one.B = B
+    dt = G.DeviceTree(one)
+    dt.prepare()
+    a, b = torch.full_like(dt.out, float("nan")), torch.full_like(dt.out, float("nan"))
+    dt.verify(out=a)
+    dt.verify(out=b, noalloc=True)
+    torch.cuda.synchronize()
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert torch.equal(a[:8].view(torch.int32), a[B // 8 * 8 - 8:B // 8 * 8].view(torch.int32))
+    d = G.make_dims(B + B // 50 + 1, T, 1, 1, 16, 16)
+    fake = [ctypes.c_void_p(0x1000)] * 10  # refused on the host
+    assert G.lib().gdn_tree_verify_noalloc(ctypes.byref(d), *fake, None) == G.GDN_EUNSUPPORTED
