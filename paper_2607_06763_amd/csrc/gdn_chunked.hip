@@ -254,11 +254,14 @@ struct GramSmem {
   static constexpr size_t diag = 2 * mat + (kHT / 64) * kDiagLds * 4;  // Gram, then per wave A and its rows' gates
   static constexpr size_t uni = planes > diag ? planes : diag;
   static constexpr size_t total = uni + size_t(kBc) * kHW * 8;  // ancestor words of block j
-  static_assert(total <= 53 * 1024, "three workgroups per CU");
+  static_assert(total <= 80 * 1024, "two workgroups per CU");
 };
 
+// Two workgroups per CU: for three (80 registers) 4 registers spill and the
+// launch takes the same time (8 x 64, 8 x 256 and 8 x 512 slots: 10.1, 44.5 and
+// 123 us).
 template <int DK, typename TIn>
-__global__ __launch_bounds__(kHT, 6) void chunk_gram_kernel(ChunkParams p) {
+__global__ __launch_bounds__(kHT, 4) void chunk_gram_kernel(ChunkParams p) {
   using SM = GramSmem<DK>;
   constexpr int KP = SM::KP, LKH = SM::LKH;
   constexpr int NQK = (2 * kBc * (DK / 4) + kHT - 1) / kHT;  // float4 of q_j and k_j per thread
