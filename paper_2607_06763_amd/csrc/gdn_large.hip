@@ -724,12 +724,13 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     for (int i = tid; i < DV * (32 - DK); i += kLT)
       s_plane[(i / (32 - DK)) * KP + plane_col(DK + i % (32 - DK))] = (_Float16)0.0f;
   }
-  // q~, and with it x and c, is taken times xunit, so that the fp16 hi + lo that
+  // q~, and with it x and c, is taken times 2^13, so that the fp16 hi + lo that
   // the products take of x and c end at 2^-38 of |q~| = 1, not at 2^-25.  For
-  // beta in [0, 2] |x| does not grow and 2^13 leaves c a factor of 4 below
-  // fp16's largest; with any other beta it may, and x has all of fp16's range.
+  // beta in [0, 2] |x| does not grow, and c stays a factor of 4 below fp16's
+  // largest; a node with any other beta on its path takes q~ as it is, and x has
+  // all of fp16's range.
+  constexpr float kUnit = 0x1p13f;
   const bool grown = __builtin_amdgcn_readfirstlane(__syncthreads_or(grows)) != 0;
-  const float xunit = grown ? 1.0f : 0x1p13f;
 
   // ---- tiles of 16 nodes, one wave each: no barrier below
   unsigned char* buf = smem + SM::plane + wave * SM::chunk;
@@ -759,9 +760,9 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // chunk's k~ while one is solved, vf the own v~ rows while the second is.
     KF kf;
     VF vf;
-    f16x8 qf[KB];   // q~ of column l16 times xunit, channel order
+    f16x8 qf[KB];   // q~ of column l16 times kUnit, channel order
     f16x4 qc[NX];   // and accumulator order
-    f32x4 x[NX], acc[NV];  // x times xunit
+    f32x4 x[NX], acc[NV];  // x times kUnit
     const int16_t* path = s_path + n0;
     const int near = path[kLTile - 1];  // parent of the tile's first node
     auto row_off = [&](const int16_t* lst) {  // of operand row l16
@@ -774,7 +775,7 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       qs.load(Fb + g * DK, uint32_t(s_row[n]) * uint32_t(2 * C), lane);
       load_k(nullptr);
 #pragma unroll
-      for (int i = 0; i < KF::NI; ++i) qs.st[i] *= (_Float16)xunit;
+      for (int i = 0; i < KF::NI; ++i) qs.st[i] *= (_Float16)kUnit;
       qs.store(buf, opaque(lane));
       wave_lds_order();
 #pragma unroll
@@ -783,7 +784,21 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
       for (int t = 0; t < NX; ++t) qc[t] = KF::slots(buf, t, l16, m);
       wave_lds_order();
     }
-    float rw = grown ? 1.0f : 0x1p-13f;  // decay of the rows walked, over xunit
+    float rw = 1.0f / kUnit;  // decay of the rows walked, over x's unit
+    if (grown) {  // uniform, rare: only the nodes below such a beta
+      bool below = false;
+      for (int a = 0; a < n0 + kLTile; ++a) {
+        const RowGate g = s_g[a];
+        below = below || (a <= n && n < g.end && (g.be < 0.0f || g.be > 2.0f));
+      }
+      if (below) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) qf[kb] *= (_Float16)(1.0f / kUnit);
+#pragma unroll
+        for (int t = 0; t < NX; ++t) qc[t] *= (_Float16)(1.0f / kUnit);
+        rw = 1.0f;
+      }
+    }
     // The substitution over one chunk of path nodes: x and rw move up by the
     // chunk; returns the value coefficients r c / (v~ row scale) of the
     // accumulator rows.  kf: the chunk's k~ rows on entry; once they are in

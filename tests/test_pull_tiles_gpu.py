@@ -299,3 +299,35 @@ def test_writes_that_grow_the_query(G, orc, beta):
     err = np.max(np.abs(dt.out.cpu().numpy() - ref)) / np.max(np.abs(ref))
     print(f"[gpu]   err {err:.3e}", flush=True)
     assert err <= 2 * O_TOL  # an error is amplified as q~ is
+
+
+@pytest.mark.parametrize("what", ["q", "alpha", "beta"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("at", [0, 7, 150])
+def test_not_finite_gates_and_queries(G, orc, what, value, at):
+    """The same for q and the gates of an early, a middle and a late node."""
+    import torch
+    T = 200
+    w = W.make_random(9210 + at, 2, T, 1, 2, 32, 32, "f32", shuffle=True)
+    ref = orc.prepare(w.parent)
+    b = 1
+    j = int(ref["order"][b, at])
+    print(f"[gpu] {what} = {value} at position {at}", flush=True)
+    dt = G.DeviceTree(w)
+    dt.prepare()
+    dt.verify()
+    torch.cuda.synchronize()
+    clean = dt.out.clone().cpu().numpy()
+    if what == "q":
+        dt.q[b, j, 0, 3] = value
+    else:
+        getattr(dt, what)[b, j, 1] = value
+    dt.verify()
+    torch.cuda.synchronize()
+    got = dt.out.cpu().numpy()
+    desc = np.array([i == j or (int(ref["anc"][b, i, j // 64]) >> (j % 64)) & 1 for i in range(T)], bool)
+    keep = np.ones(got.shape[:3], bool)
+    for h in [0, 1] if what == "q" else [1]:
+        assert not np.isfinite(got[b, j, h]).all()
+        keep[b, desc, h] = False
+    np.testing.assert_array_equal(got[keep].view(np.int32), clean[keep].view(np.int32))
