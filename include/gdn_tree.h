@@ -182,9 +182,11 @@ int gdn_tree_verify_noalloc(const gdn_dims* dims, const void* meta, const void* 
  * layouts, outputs and errors are those of gdn_tree_verify (any supported
  * dk, dv and T).  Needs a workspace of about B (T (C + Hv dv) + 1024 n (2 Hv +
  * (n - 1) Hk)) 4 bytes, n = ceil(T / 32), cached per (device, stream) like
- * gdn_tree_verify's above 128 slots.  Its cost does not
- * grow with the depth of the tree, while gdn_tree_verify's grows with the sum
- * of the path lengths. */
+ * gdn_tree_verify's above 128 slots (the pairs of blocks without an ancestor
+ * have room in it, too).  Its cost grows with the pairs of 32-slot blocks of
+ * which one holds an ancestor of a node of the other; gdn_tree_verify's up to
+ * 128 slots with the sum of the path lengths, above with the number of 16-node
+ * path chunks of its 16-node tiles. */
 int gdn_tree_verify_chunked(const gdn_dims* dims, const void* meta, const void* q, const void* k,
                             const void* v, const void* alpha, const void* beta,
                             const float* conv_w, const float* conv_state, const float* S0,

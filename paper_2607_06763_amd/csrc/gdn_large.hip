@@ -36,13 +36,15 @@
 // it, 4.4 GB per launch at 32 trees x 512 slots, 16 / 48 heads of 128, and
 // spent two thirds of its instructions on it.  A tile reads the union of its
 // nodes' paths, its own rows plus one chain, once.  That launch (with the
-// commit of the fused step) went from 503 to 310 us, verification alone at 16
-// x 250 slots, 16 / 32 heads, from 71 to 48 us.  Of this, rows loaded whole
-// (RowStage) instead of one per lane are 363 -> 310 us at 512 slots.  128
-// registers and 80 KB keep two workgroups on a CU: every variant that spilled
-// more or ran one lost (the values' accumulators live during the
-// substitutions: 62 spills, 647 us).  Writing the outputs through LDS in whole
-// 256-byte runs changed nothing (B = 32) or lost 3 us (B = 1).
+// commit of the fused step) went from 480 to 353 us, verification alone at 16
+// x 250 slots, 16 / 32 heads, from 74 to 54 us (both forms in one run); bound
+// by the VALU work around the MFMA and the fp32 products of the values.  128
+// registers and 80 KB keep two workgroups on a CU, with 9 (fused: 11) spilled
+// registers at dk = dv = 128 and none below.  With the values still in fp16,
+// rows loaded whole (RowStage) instead of one per lane were 363 -> 310 us at
+// 512 slots, the values' accumulators live during the substitutions 62 spills
+// and 647 us, and outputs through LDS in whole 256-byte runs changed nothing (B
+// = 32) or lost 3 us (B = 1).
 // The fused decode step (Sec. 3.4.2) runs the conv-state shift of the
 // previous step's commit first, the features on the committed conv state,
 // and pull_kernel<..., FUSED>, which commits the previous accepted path into
@@ -500,7 +502,7 @@ __global__ __launch_bounds__(kFT) void feat_kernel(LargeParams p, int DV, int nc
 }
 
 // ---------------------------------------------------------------------------
-// Pull-back along gathered features + fp16 MFMA readout
+// Pull-back by tiles of 16 nodes + fp16 MFMA readout
 // ---------------------------------------------------------------------------
 // Two workgroups per CU: at most 80 KB each.
 template <int DK, int DV>
@@ -539,7 +541,8 @@ __device__ __forceinline__ void ld_f(const float* src, float (&x)[N]) {
 // 16 rows of D halves on their way to LDS: a load covers whole rows (16 bytes
 // per lane, D / 8 lanes per row), which keeps the address lanes of the vector
 // cache few: with a row per lane a load took 64 lookups and the launch was
-// bound by them (32 x 512 slots: 295 us alone, 243 with whole rows).  In LDS row rho is at rho * 2 D bytes, its 32-byte granules
+// bound by them (32 x 512 slots, no commit, values in fp16: 295 us, 243 with
+// whole rows).  In LDS row rho is at rho * 2 D bytes, its 32-byte granules
 // swizzled by rho.
 template <int D>
 struct RowStage {
@@ -903,9 +906,9 @@ __global__ __launch_bounds__(kLT, 4) void pull_kernel(LargeParams p) {
     // acc (+)= V^T mm over the chunk, whose v~ rows are in vf.  In fp32: the
     // coefficients of a path differ without bound, and a small one counts in
     // the channels where the rows of the large ones are 0.  As fp16 hi + lo
-    // under one scale per node (2 products instead of 4) the launch took 310
-    // instead of 335 us at 32 x 512 (with the commit), 48 instead of 54 at 16
-    // x 250, and lost what was below 2^-25 of the node's largest.  The rate of
+    // under one scale per node (2 products instead of 4) the call took 506
+    // instead of 529 us at 32 x 512 (with the commit), 87 instead of 93 at 16 x
+    // 250, and lost what was below 2^-25 of the node's largest.  The rate of
     // the fp32 products is what they cost: 2 or 4 channel tiles in turn took as
     // long.
     auto values = [&](const int16_t* lst, f32x4 mm, bool marked, auto ahead) {

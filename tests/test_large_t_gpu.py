@@ -1,4 +1,4 @@
-"""GPU parity for trees of 129..512 slots (feature workspace + gathered
+"""GPU parity for trees of 129..512 slots (feature workspace + tiled
 pull-back verify, commit over paths of up to 512 nodes, and the step as
 commit then verify), through the C ABI against the CPU oracle.
 
